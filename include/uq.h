@@ -164,9 +164,11 @@ uq_status uq_prepare_query(const uq_cache_desc *desc, const void *q, uq_dtype q_
 size_t uq_decode_workspace_bytes(const uq_cache_desc *desc, int32_t batch, int32_t num_q_heads,
                                  int32_t max_context, int32_t partition_tokens);
 
-/* Partition length (tokens) the library picks when partition_tokens == 0:
- * the longest (1024 .. 16384) that still gives the 256 compute units two
- * blocks each.  A block serves one KV head, or two at head size 64 when the
+/* The library's default partition length (tokens): the longest (1024 ..
+ * 16384) that still gives the 256 compute units two blocks each when every
+ * context has max_context tokens.  It sizes the workspace of a call with
+ * partition_tokens == 0; how such a call (or one that passes this value) cuts
+ * its contexts is described at uq_decode_attention.  A block serves one KV head, or two at head size 64 when the
  * group size is at most 8 and num_kv_heads is even (the kernel then treats
  * the pair as one 128-channel head with a block-diagonal query operand). */
 int32_t uq_default_partition(const uq_cache_desc *desc, int32_t batch, int32_t num_q_heads, int32_t max_context);
@@ -182,7 +184,13 @@ int32_t uq_default_partition(const uq_cache_desc *desc, int32_t batch, int32_t n
  * blocks of 8 exist and there are 16 partitions or more, else 4) -- one
  * wave per partition, a block taking W consecutive partitions of one
  * sequence and kv head and reducing their partials into one before the
- * merge.  The result does not depend on the grid beyond rounding.
+ * merge.  With the default partition (0, or its value), more than one of
+ * them, no shared prefix and up to 256 sequences, the block grid instead
+ * shares its rows among the sequences by their lengths, read on the device:
+ * the kernels cut every context into equal partitions of the shortest length
+ * for which the rows suffice, so that a ragged batch, or one far below
+ * max_context, still fills the GPU.  The result does not depend on the grid
+ * beyond rounding.
  *   q             : [batch][num_q_heads][128].  F32/BF16/F16: rotated and
  *                   cast to FP8 inside the call.  FP8_E4M3: already
  *                   prepared by uq_prepare_query.
@@ -193,7 +201,8 @@ int32_t uq_default_partition(const uq_cache_desc *desc, int32_t batch, int32_t n
  *                   device read.  Lengths above it are clamped to it.
  *   softmax_scale : multiplies q.k (usually 1/sqrt(128)); finite and > 0.
  *   partition_tokens : context tokens per split-context partition, a
- *                   multiple of 16 (whole pages), or 0 for the default.
+ *                   multiple of 16 (whole pages), or 0 for the default
+ *                   (the balanced split above).
  *   workspace     : >= uq_decode_workspace_bytes(...) bytes of device
  *                   memory, 16-byte aligned, no initial contents required.
  *                   Calls that share a workspace must not run concurrently.

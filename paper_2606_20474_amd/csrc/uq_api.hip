@@ -71,6 +71,24 @@ int64_t num_partitions(int32_t max_context, int32_t part) {
     return max_context > 0 ? (int64_t(max_context) + part - 1) / part : 1;
 }
 
+// Rows of the balanced split (0: one partition length for the launch) of a
+// call whose partition is the library's default, whether asked for by 0 or by
+// its value.  Never more than the default partition's own rows, which size
+// the workspace.  512 blocks, two per CU, are enough where the sequences are
+// few (a single 120k context, 8 kv heads: 27.6 us with 512 blocks, 28.7 with
+// its 472 default partitions, 33 with 944), and four rows per sequence where
+// they alone fill the chip (64 sequences of 0.3k-64k tokens, 8 kv heads: 128 us
+// with 2048 blocks, 130 with 1024, 269 with 512).  The planner's lanes hold 256
+// lengths, whose sum and rounding stay within 30 bits.
+int32_t split_rows(int32_t batch, int32_t block_heads, int32_t max_context, int32_t part) {
+    const int64_t np = num_partitions(max_context, part);
+    if (np <= 1 || part != pick_partition(batch, block_heads, max_context)) return 0;
+    if (batch > uq::kPlanBatch || int64_t(batch) * max_context >= (int64_t(1) << 30)) return 0;
+    int64_t rows = 2 * uq::kNumCus / block_heads;
+    rows = rows > 4 * int64_t(batch) ? rows : 4 * int64_t(batch);
+    return int32_t(rows < np * batch ? rows : np * batch);
+}
+
 // Workspace of a decode call: the partial rows (accumulators, then the
 // (max, sum) pairs); a cascade call (extra_slots > 0: its prefix
 // partitions) adds its row list, 16 bytes per context row (partition,
@@ -148,6 +166,9 @@ uq_status make_decode_params(const uq_cache_desc* desc, const void* q, uq_dtype 
     p.suffix_partitions = int32_t(np_ctx);
     p.allow_wave_parts = 1;
     p.wave_parts = 0;
+    p.plan_rows = extra_slots > 0 ? 0 : split_rows(batch, block_heads(desc, num_q_heads), max_context, part);
+    p.plan_inv_rows = p.plan_rows > 0 ? 1.0f / float(p.plan_rows) : 0.0f;
+    p.plan_inv_free = p.plan_rows > batch ? 1.0f / float(p.plan_rows - batch) : 0.0f;
     p.probe_sink = nullptr;
     return UQ_OK;
 }
@@ -484,6 +505,7 @@ uq_status uq_decode_attention_scaled_pv(const uq_cache_desc* desc, const void* q
     if (desc->head_dim != kHeadDim) return UQ_ERR_UNSUPPORTED;
     if (p.partition_tokens % 32 != 0) return UQ_ERR_INVALID_ARGUMENT;   // whole page pairs only
     p.allow_wave_parts = 0;   // the prototype's grid is one block per partition
+    p.plan_rows = 0;
     s = from_hip(uq::launch_decode_partials_mxpv(p, static_cast<hipStream_t>(stream)));
     if (s != UQ_OK) return s;
     return from_hip(uq::launch_decode_merge(p, static_cast<hipStream_t>(stream)));

@@ -24,6 +24,7 @@ struct TqTables {
     uint32_t lut[8];
 };
 constexpr int kNumCus = 256;     // compute units of an MI355X (8 XCDs x 32)
+constexpr int kPlanBatch = 256;  // sequences a balanced split can hold
 constexpr int kTqBlock = 2368;   // bytes per (page, kv head) of the Ultra-TQ cache
 constexpr int kTqMeta = 2048;    // offset of the norms and (scale, zero) words in a block
 
@@ -119,6 +120,12 @@ struct DecodeParams {
     // allow_wave_parts.
     int32_t allow_wave_parts;
     int32_t wave_parts;
+    // balanced split of the contexts (see SplitPlan in uq_decode.hip): the rows
+    // the whole batch shares, 0 for one partition length per launch, and
+    // 1 / plan_rows and 1 / (plan_rows - batch)
+    int32_t plan_rows;
+    float plan_inv_rows;
+    float plan_inv_free;
     // the page-gather probe's checksums, one per wave of the partition
     // launch, sink[block * W + wave] (set only by launch_gather_probe)
     uint32_t* probe_sink;

@@ -1,0 +1,109 @@
+"""The balanced split of ragged batches (calls that leave the partition to the
+library) and the merge of its partials, against the fixed partitions of the
+same kernels.
+
+A call with partition 0 cuts every context by the plan the device makes from
+the lengths; the same call with an explicit partition that is not the
+default keeps one partition length per launch, the path the other tests hold
+to the oracle.  Batches of 1, 64 (one length per planner lane), 65 and 256
+(up to four), and 257 (fixed partitions again); lengths at the edges of the
+plan's 128-token unit, empty contexts, all lengths equal, one long context
+among short ones; a bound of the lengths far above them; every cache format
+and head size.  Both paths round P to two BF16 terms, |error| <= 2^-16 |P|, so
+an output element differs by at most 2 * 2^-16 * max|V| plus fp32 sums of a few
+units of 2^-24: held to 2^-14 * max|V| over the cache.
+  * the workspace is full of 0xFF bytes (NaN partials) before the call;
+  * the two launches called one by one, and the default partition passed by
+    its value, give the same bits.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2606_20474_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [0, 1, 16, 127, 128, 129, 255, 256, 257, 383, 384, 385, 1023, 1024, 1025, 2047]
+V_MAX = 6.0 * 20.0   # N(0, 1) draws below 6, outlier channels times 20; a rotated V is a sum of them over sqrt(d)
+
+
+@pytest.fixture(scope="module")
+def uq():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2606_20474_amd import uq as mod
+    return mod
+
+
+def lens(kind, batch, top):
+    rng = np.random.default_rng(batch)
+    if kind == "edges":
+        ctx = (EDGES * (batch // len(EDGES) + 1))[:batch - 1] + [top]
+        return [int(c) for c in rng.permutation(ctx)]
+    if kind == "equal":
+        return [top] * batch
+    if kind == "one-long":
+        return [top] + [int(c) for c in rng.integers(1, 200, batch - 1)]
+    return [0] * (batch - 1) + [top]   # "empty"
+
+
+@pytest.mark.parametrize("batch,hq,hkv,kind,top,bound,fmt,d", [
+    (1, 8, 1, "equal", 5000, 0, "fp4", 128),
+    (1, 16, 8, "equal", 4097, 131072, "fp4", 128),
+    (3, 12, 2, "one-long", 20011, 65536, "fp4", 128),
+    (4, 16, 2, "empty", 3000, 0, "fp4", 128),
+    (64, 8, 1, "edges", 6001, 0, "fp4", 128),
+    (65, 8, 1, "edges", 6001, 16384, "fp4", 128),
+    (130, 6, 1, "one-long", 9000, 0, "fp4", 128),
+    (256, 4, 2, "edges", 4099, 0, "fp4", 128),
+    (257, 4, 2, "edges", 4099, 0, "fp4", 128),
+    (12, 16, 2, "edges", 5000, 0, "fp8", 128),
+    (12, 16, 2, "edges", 5000, 0, "bf16", 128),
+    (12, 16, 2, "edges", 5000, 0, "tq4", 128),
+    (20, 8, 2, "edges", 5000, 0, "fp4", 64),
+    (20, 5, 1, "edges", 5000, 16384, "fp4", 64),
+    (20, 12, 1, "edges", 5000, 0, "fp4", 64),
+    (12, 8, 2, "edges", 5000, 0, "fp4", 256),
+])
+def test_default_split_equals_fixed_partitions(uq, batch, hq, hkv, kind, top, bound, fmt, d):
+    dev = torch.device("cuda:0")
+    print(f"balanced split: B={batch} {hq}/{hkv} heads of {d}, {kind} up to {top}, bound {bound}, {fmt}", flush=True)
+    wl = workloads.custom(batch, hq, hkv, lens(kind, batch, top), seed=batch, paging="random", head_dim=d)
+    max_context = max(bound, wl.max_context)
+    pt = np.zeros((batch, -(-max_context // 16)), dtype=np.int32)
+    pt[:, :wl.page_table.shape[1]] = wl.page_table
+    pt, ctx = torch.as_tensor(pt, device=dev), torch.as_tensor(wl.context_lens, device=dev)
+    q = wl.q.to(dev)
+    if fmt == "fp4":
+        desc = uq.CacheDesc(num_kv_heads=hkv, num_pages=wl.num_pages, head_dim=d)
+        bufs, write, attend = desc.alloc_pools(dev, fill=0), uq.quantize_kv, uq.decode_attention
+        part, nbytes = uq.default_partition(desc, batch, hq, max_context), uq.workspace_bytes
+        partials, merge = uq.decode_partials, uq.decode_merge
+    else:
+        desc = uq.RefCacheDesc(num_kv_heads=hkv, num_pages=wl.num_pages, fmt=fmt, k_scale=0.3, v_scale=0.3)
+        bufs, write, attend = (desc.alloc_cache(dev, fill=0),), uq.ref_write_kv, uq.ref_decode_attention
+        geometry = uq.CacheDesc(num_kv_heads=hkv, num_pages=wl.num_pages)
+        part, nbytes = uq.default_partition(geometry, batch, hq, max_context), uq.ref_workspace_bytes
+        partials, merge = uq.ref_decode_partials, uq.ref_decode_merge
+    for key, lo, hi, row in wl.segments():
+        k, v = wl.kv(key, lo, hi, device=dev)
+        write(desc, k, v, torch.as_tensor(wl.slots(key, lo, hi, row), device=dev), *bufs)
+    ws = torch.empty(nbytes(desc, batch, hq, max_context, 0), dtype=torch.uint8, device=dev)
+
+    def run(p, workspace=None):
+        return attend(desc, q, *bufs, pt, ctx, max_context, d ** -0.5, p, workspace=workspace)
+
+    ws.fill_(0xFF)
+    got = run(0, ws)
+    ref = run(512 if part != 512 else 1024)
+    ws.fill_(0xFF)
+    two = torch.full_like(got, float("nan"))
+    partials(desc, q, *bufs, pt, ctx, max_context, d ** -0.5, part, ws, two)
+    merge(desc, batch, hq, ctx, max_context, part, ws, two)
+    torch.cuda.synchronize()
+    assert torch.equal(two, got) and torch.equal(run(0), got)
+    assert torch.isfinite(got).all()
+    err = float((got - ref).abs().max())
+    print(f"  max difference {err:.3e}", flush=True)
+    assert err <= V_MAX * 2.0 ** -14
+    assert torch.all(got[ctx == 0] == 0)

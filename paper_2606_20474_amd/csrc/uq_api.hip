@@ -154,7 +154,9 @@ uq_status make_decode_params(const uq_cache_desc* desc, const void* q, uq_dtype 
     p.out_dtype = out_dtype == UQ_F32 ? 0 : 1;
     p.rotate_v = desc->rotate_v != 0;
     p.head_dim = desc->head_dim;
-    p.kv_fmt = desc->head_dim == 64 ? (paired_heads(desc, num_q_heads) ? uq::kFp4d64x2 : uq::kFp4d64)
+    p.kv_fmt = desc->head_dim == 64 ? (paired_heads(desc, num_q_heads)            ? uq::kFp4d64x2
+                                       : num_q_heads <= 8 * desc->num_kv_heads ? uq::kFp4d64p2
+                                                                               : uq::kFp4d64)
                : desc->head_dim == 256 ? uq::kFp4d256 : uq::kFp4;
     p.out_scale = 1.0f;
     p.prefix_pages = nullptr;

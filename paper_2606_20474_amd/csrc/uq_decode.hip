@@ -5,8 +5,9 @@
 // between them measures the format, not the kernel:
 //   kFp4   the UltraQuant cache: FP4 E2M1 codes + UE8M0 scales per 32
 //          channels, K (and V with rotate_v) Walsh-Hadamard rotated
-//          (kFp4d64x2, kFp4d64, kFp4d256: the same cache at head sizes 64
-//          and 256; kFp4d64x2 takes two KV heads per block);
+//          (kFp4d64x2, kFp4d64p2, kFp4d64, kFp4d256: the same cache at head
+//          sizes 64 and 256; kFp4d64x2 takes two KV heads per block, kFp4d64p2
+//          two page pairs of one head at a time);
 //   kFp8   a plain FP8 E4M3 cache with one scale per tensor;
 //   kBf16  a plain BF16 cache;
 //   kTq4   the Ultra-TQ codebook cache (rotated K as 4-bit indices into 16
@@ -126,13 +127,31 @@ template <> struct Fmt<kFp4d64x2> {
     static constexpr int kWaves = 4;
     static constexpr int kOccupancy = 4;
 };
-template <int F> constexpr bool is_fp4() { return F == kFp4 || F == kFp4d64 || F == kFp4d256 || F == kFp4d64x2; }
-template <int F> constexpr int head_dim_of() {
-    return (F == kFp4d64 || F == kFp4d64x2) ? 64 : F == kFp4d256 ? 256 : 128;
+// Head size 64, one KV head (an odd number of them, as in a tensor-parallel
+// share), group size at most 8: the same stage and arithmetic with two page
+// pairs of the head, A and then B, in the place of the two heads.  Columns 8..15
+// repeat the query heads on k 64..127, so columns 0..7 hold the scores of pair
+// A's tokens and columns 8..15 those of pair B's; the two column sets run their
+// own online softmax and are merged like two waves at the end.  One block of
+// kFp4d64 spends the same instructions on half the tokens (a ragged batch
+// of 64, 8 query heads, 72 MB: 28.0 us with kFp4d64, 19.0 us with this).
+template <> struct Fmt<kFp4d64p2> {
+    static constexpr int kTile = 1024;
+    static constexpr int kScaleBlock = 2 * kTileScales;
+    static constexpr int kWaves = 4;
+    static constexpr int kOccupancy = 4;
+};
+template <int F> constexpr bool is_fp4() {
+    return F == kFp4 || F == kFp4d64 || F == kFp4d256 || F == kFp4d64x2 || F == kFp4d64p2;
 }
-// The register and operand formats: the paired head-size-64 stage is read
-// and computed as a head-size-128 FP4 stage.
-template <int F> constexpr int regs_fmt() { return F == kFp4d64x2 ? kFp4 : F; }
+template <int F> constexpr int head_dim_of() {
+    return (F == kFp4d64 || F == kFp4d64x2 || F == kFp4d64p2) ? 64 : F == kFp4d256 ? 256 : 128;
+}
+// The register and operand formats: the head-size-64 stages of two heads or
+// two page pairs are read and computed as a head-size-128 FP4 stage.
+template <int F> constexpr int regs_fmt() { return F == kFp4d64x2 || F == kFp4d64p2 ? kFp4 : F; }
+// Pages a wave takes per iteration.
+template <int F> constexpr int pages_per_iter() { return F == kFp4d64p2 ? 4 : 2; }
 // Ultra-TQ: per page 1 KiB of K indices, 1 KiB of V codes and 320 bytes of
 // norms and (scale, zero) words ("scale block").
 template <> struct Fmt<kTq4> {
@@ -219,18 +238,18 @@ __device__ __forceinline__ void split_p(float a, float b, uint32_t& hi, uint32_t
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
-// Page ids of one wave, 64 at a time: lane j holds the id of the wave's
-// page 2*(32*chunk + j/2) + j%2 counted in its own iteration order
-// (iteration k of wave w covers partition pages 2*(w + W*k) and +1).  The
-// range check (clamp_ids) follows once the ids are in registers.
-template <int W>
+// Page ids of one wave, 64 at a time: lane j holds the id of page j % P of
+// the wave's iteration 64 / P * chunk + j / P, P pages per iteration (iteration
+// k of wave w covers partition pages P * (w + W * k) .. + P - 1).  The range
+// check (clamp_ids) follows once the ids are in registers.
+template <int W, int P>
 __device__ __forceinline__ int ids_page(int wave, int chunk, int lane) {
-    return 2 * (wave + W * (32 * chunk + (lane >> 1))) + (lane & 1);
+    return P * (wave + W * (64 / P * chunk + lane / P)) + lane % P;
 }
-template <int W>
+template <int W, int P = 2>
 __device__ __forceinline__ int32_t load_page_ids(const int32_t* __restrict__ pt_row, int first_page, int n_pages,
                                                  int wave, int chunk, int lane) {
-    const int pg = ids_page<W>(wave, chunk, lane);
+    const int pg = ids_page<W, P>(wave, chunk, lane);
     int32_t id = 0;
     if (pg < n_pages) id = pt_row[first_page + pg];
     return id;
@@ -240,10 +259,10 @@ __device__ __forceinline__ int32_t load_page_ids(const int32_t* __restrict__ pt_
 // them into registers would make the wave wait for this load, and with it
 // for every page copy in flight, when their values are first used.  Lanes
 // past the partition read its first entry (their ids are never used).
-template <int W>
+template <int W, int P = 2>
 __device__ __forceinline__ void copy_page_ids(uint8_t* slot, const int32_t* __restrict__ pt_row, int first_page,
                                               int n_pages, int wave, int chunk, int lane) {
-    const int pg = ids_page<W>(wave, chunk, lane);
+    const int pg = ids_page<W, P>(wave, chunk, lane);
     __builtin_amdgcn_global_load_lds(pt_row + first_page + (pg < n_pages ? pg : 0), (lds_ptr_t)slot, 4, 0, 0);
 }
 // This lane's id from the wave's LDS slot; the caller has waited for the copy.
@@ -334,6 +353,29 @@ __device__ __forceinline__ void stage_issue(uint8_t* stage, const uint8_t* __res
             const uint8_t* sc = scales + (t >> 1) * SB + 16 * (lane % (SB / 16));
             __builtin_amdgcn_global_load_lds(sc, (lds_ptr_t)(stage + 4 * T), 16, 0, AUX);
         }
+    }
+}
+
+// The same for kFp4d64p2: page pair A (tiles a0, a1: K tiles in 512-byte tiles)
+// and pair B (b0, b1) of one head in the stage layout of kFp4d64x2.
+template <int AUX = kPageStream>
+__device__ __forceinline__ void stage_issue_pairs(uint8_t* stage, const uint8_t* __restrict__ codes,
+                                                  const uint8_t* __restrict__ scales, int64_t a0, int64_t a1,
+                                                  int64_t b0, int64_t b1, int lane) {
+    const int u = lane & 15, r = lane >> 4;
+    const int64_t ko = 16 * (lane & 31);
+    const int64_t vo = 512 + 16 * (8 * r + (u & 7));
+    const bool kb = lane >= 32, vb = u >= 8;
+    __builtin_amdgcn_global_load_lds(codes + (kb ? b0 : a0) * 512 + ko, (lds_ptr_t)stage, 16, 0, AUX);
+    __builtin_amdgcn_global_load_lds(codes + (vb ? b0 : a0) * 512 + vo, (lds_ptr_t)(stage + 1024), 16, 0, AUX);
+    __builtin_amdgcn_global_load_lds(codes + (kb ? b1 : a1) * 512 + ko, (lds_ptr_t)(stage + 2048), 16, 0, AUX);
+    __builtin_amdgcn_global_load_lds(codes + (vb ? b1 : a1) * 512 + vo, (lds_ptr_t)(stage + 3072), 16, 0, AUX);
+    if (lane < 16) {
+        // 16-byte unit j of a page's 128-byte block: K_A K_A K_B K_B V_A V_A V_B V_B
+        const int j = lane & 7;
+        const int64_t t = lane < 8 ? ((j & 2) ? b0 : a0) : ((j & 2) ? b1 : a1);
+        const uint8_t* sc = scales + (t >> 1) * 64 + (j < 4 ? 0 : 32) + 16 * (j & 1);
+        __builtin_amdgcn_global_load_lds(sc, (lds_ptr_t)(stage + 4096), 16, 0, AUX);
     }
 }
 
@@ -961,14 +1003,17 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
     static_assert(S == 2 || S == 4, "ring slots");
     static_assert(W == 2 || W == 4 || W == 8, "waves per block");
     static_assert(!PROBE || is_fp4<F>(), "the page-gather probe follows the FP4 kernels");
-    static_assert(!WP || (head_dim_of<F>() == 128 && F != kFp4d64x2), "one wave per partition: head size 128");
+    static_assert(!WP || head_dim_of<F>() == 128, "one wave per partition: head size 128");
     constexpr int kThreads = 64 * W;
     constexpr int kStage = stage_bytes<F>();
     constexpr int kQRounds = (256 + kThreads - 1) / kThreads;   // 16 threads per query row, 16 rows
     constexpr int D = head_dim_of<F>();         // head size
     constexpr int N = D / 16;                   // channels per lane of a 16-lane row
     constexpr bool kPair = F == kFp4d64x2;      // two kv heads of 64 per block
-    constexpr int DA = kPair ? 128 : D;         // channels of the accumulators
+    constexpr bool kTwo = F == kFp4d64p2;       // two page pairs of one kv head of 64 per iteration
+    constexpr int DA = kPair || kTwo ? 128 : D;   // channels of the accumulators
+    constexpr int kPages = pages_per_iter<F>();   // pages (of 16 tokens) per iteration
+    constexpr int kSpan = 16 * kPages;
     constexpr int kAccTiles = DA == 256 ? 16 : 8;   // PV output tiles of 16 channel blocks x 16 heads
     // Linear block order: kv head fastest, then sequence, then partition.
     // Workgroups go to the 8 XCDs round-robin by linear id, so this spreads
@@ -1105,6 +1150,11 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
             rhq = (2 * hk + (r >> 3)) * G + (r & 7);
             return (r & 7) < G;
         }
+        if constexpr (kTwo) {
+            rb = b;
+            rhq = hk * G + (r & 7);
+            return (r & 7) < G;
+        }
         if (pre) {
             const int f = 16 * chunk + r;
             rb = f / G;
@@ -1208,10 +1258,10 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
     // ---------------- page walk set-up and the first two stages in flight
     const int first_page = start >> 4;
     const int n_pages = (end - start + 15) >> 4;
-    const int n_iter = (n_pages + 1) >> 1;
+    const int n_iter = (n_pages + kPages - 1) / kPages;
     const int n_local = WP ? n_iter : wave < n_iter ? (n_iter - wave + W - 1) / W : 0;
     // page-walk order: iteration k of the wave covers partition pages
-    // 2 * (woff + ws * k) and + 1
+    // kPages * (woff + ws * k) and the next ones
     constexpr int ws = WP ? 1 : W;
     const int woff = WP ? 0 : wave;
     const int32_t* pt_row = pre ? p.prefix_pages : p.page_table + int64_t(b) * p.max_pages_per_seq;
@@ -1239,27 +1289,34 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
 
     uint8_t* ids_slot = ids_lds + wave * kIdsSlot;
     const uint32_t ids_addr = uint32_t(reinterpret_cast<uintptr_t>((lds_ptr_t)ids_slot));
+    constexpr int kIdIters = 64 / kPages;   // iterations per chunk of 64 page ids
     int32_t ids = 0;
     if (n_local > 0) {
-        ids = load_page_ids<ws>(pt_row, first_page, n_pages, woff, 0, lane);
-        if (n_local > 32) copy_page_ids<ws>(ids_slot, pt_row, first_page, n_pages, woff, 1, lane);
+        ids = load_page_ids<ws, kPages>(pt_row, first_page, n_pages, woff, 0, lane);
+        if (n_local > kIdIters) copy_page_ids<ws, kPages>(ids_slot, pt_row, first_page, n_pages, woff, 1, lane);
     }
+    // copy the pages whose ids sit at lanes kPages * i .. of `ids` into slot s
+    auto issue = [&](int s, int i) {
+        const int64_t id0 = __builtin_amdgcn_readlane(ids, kPages * i);
+        const int64_t id1 = __builtin_amdgcn_readlane(ids, kPages * i + 1);
+        const int64_t t0 = id0 * tiles_per_page + head_tile, t1 = id1 * tiles_per_page + head_tile;
+        if constexpr (kTwo) {
+            const int64_t id2 = __builtin_amdgcn_readlane(ids, kPages * i + 2);
+            const int64_t id3 = __builtin_amdgcn_readlane(ids, kPages * i + 3);
+            stage_issue_pairs(ring + s * kStage, p.codes, p.scales, t0, t1, id2 * tiles_per_page + head_tile,
+                              id3 * tiles_per_page + head_tile, lane);
+        } else {
+            if (pre) stage_issue<F, kPageShared>(ring + s * kStage, p.codes, p.scales, t0, t1, lane);
+            else stage_issue<F, kPageStream>(ring + s * kStage, p.codes, p.scales, t0, t1, lane);
+        }
+    };
     // The query, the new token and the page ids are in registers before the
     // first page copies are issued (one wait for all of them, so that the
     // query transform below overlaps the copies instead of waiting for them).
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     ids = clamp_ids(ids, p.num_pages);
     if (n_local > 0) {
-        for (int s = 0; s < S && s < n_local; ++s) {
-            const int64_t id0 = __builtin_amdgcn_readlane(ids, 2 * s);
-            const int64_t id1 = __builtin_amdgcn_readlane(ids, 2 * s + 1);
-            if (pre)
-                stage_issue<F, kPageShared>(ring + s * kStage, p.codes, p.scales, id0 * tiles_per_page + head_tile,
-                                            id1 * tiles_per_page + head_tile, lane);
-            else
-                stage_issue<F, kPageStream>(ring + s * kStage, p.codes, p.scales, id0 * tiles_per_page + head_tile,
-                                            id1 * tiles_per_page + head_tile, lane);
-        }
+        for (int s = 0; s < S && s < n_local; ++s) issue(s, s);
     }
 
     // ---------------- query prologue: transform and store in B-operand order
@@ -1288,10 +1345,10 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
                 }
             }
             *reinterpret_cast<uint4*>(q_lds + ((qL >> 2) * 64 + (qL & 3) * 16 + qr) * 16) = w;
-        } else if constexpr (kPair) {
-            // rotated (64-point) and cast to FP8: rows 0..7 (head A) on k
-            // 0..63, rows 8..15 (head B) on k 64..127 of the B operand (layout
-            // below); the other half of each row stays zero
+        } else if constexpr (kPair || kTwo) {
+            // rotated (64-point) and cast to FP8: rows 0..7 (head or page pair
+            // A) on k 0..63, rows 8..15 (B) on k 64..127 of the B operand
+            // (layout below); the other half of each row stays zero
             uint32_t wq = 0u;
             if (qvalid) {
                 wht_x<N>(qx[h], qL);
@@ -1424,21 +1481,14 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
         if (k + S < n_local) {
             // refill this slot with iteration k+S while iteration k computes
             const int kn = k + S;
-            if ((kn & 31) == 0) {
+            if (kn % kIdIters == 0) {
                 // the next chunk's copy is older than every stage in flight,
                 // so the wait at the top of this iteration covered it
                 ids = clamp_ids(read_page_ids(ids_addr, lane), p.num_pages);
-                if (kn + 32 < n_local) copy_page_ids<ws>(ids_slot, pt_row, first_page, n_pages, woff, (kn >> 5) + 1, lane);
+                if (kn + kIdIters < n_local)
+                    copy_page_ids<ws, kPages>(ids_slot, pt_row, first_page, n_pages, woff, kn / kIdIters + 1, lane);
             }
-            const int s = 2 * (kn & 31);
-            const int64_t id0 = __builtin_amdgcn_readlane(ids, s);
-            const int64_t id1 = __builtin_amdgcn_readlane(ids, s + 1);
-            if (pre)
-                stage_issue<F, kPageShared>(ring + slot * kStage, p.codes, p.scales, id0 * tiles_per_page + head_tile,
-                                            id1 * tiles_per_page + head_tile, lane);
-            else
-                stage_issue<F, kPageStream>(ring + slot * kStage, p.codes, p.scales,
-                                            id0 * tiles_per_page + head_tile, id1 * tiles_per_page + head_tile, lane);
+            issue(slot, kn % kIdIters);
         }
 
         if constexpr (PROBE) {
@@ -1461,8 +1511,10 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
             vs1 = c.vs[1];
         }
         const int it = woff + ws * k;
-        const int tok0 = start + 32 * it + 4 * g4;   // token of x[0]; x[4] is tok0 + 16
-        if (__builtin_amdgcn_ballot_w64(start + 32 * it + 32 > lim) != 0) {
+        // token of x[0]; x[4] is tok0 + 16 (kTwo: columns 8..15 and channel
+        // blocks 8..15 belong to the second page pair)
+        const int tok0 = start + kSpan * it + 4 * g4 + (kTwo && n >= 8 ? 32 : 0);
+        if (__builtin_amdgcn_ballot_w64(start + kSpan * it + kSpan > lim) != 0) {
             // scores past the column's last token (the partition end, or a
             // prefix column's own length)
 #pragma unroll
@@ -1470,7 +1522,7 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
                 if (tok0 + i >= lim) x[i] = -__builtin_inff();
                 if (tok0 + 16 + i >= lim) x[4 + i] = -__builtin_inff();
             }
-            if (start + 32 * it + 32 > end) {
+            if (start + kSpan * it + kSpan > end) {
                 // tokens past the end: no column reads their V
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -1616,16 +1668,19 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
         const int r = (tid >> 4) + h * (kThreads / 16);   // query row of the block
         const int L = tid & 15;                           // channels N L .. N L + N - 1
         int rb, hq;
-        if (r >= 16 || !row_of(r, rb, hq)) continue;     // whole 16-lane rows skip together
+        // whole 16-lane rows skip together
+        if (r >= (kTwo ? 8 : 16) || !row_of(r, rb, hq)) continue;
+        // kTwo: row r + 8 holds the second page pairs' part of row r
+        constexpr int H = kTwo ? 2 : 1;
         float M = red_m[0][r];
 #pragma unroll
-        for (int w = 1; w < W; ++w) M = __builtin_fmaxf(M, red_m[w][r]);
-        float f[W];
+        for (int w = 1; w < H * W; ++w) M = __builtin_fmaxf(M, red_m[w % W][r + 8 * (w / W)]);
+        float f[H * W];
         float lsum = 0.f;
 #pragma unroll
-        for (int w = 0; w < W; ++w) {
-            f[w] = __builtin_amdgcn_exp2f(red_m[w][r] - M);
-            lsum += f[w] * red_l[w][r];
+        for (int w = 0; w < H * W; ++w) {
+            f[w] = __builtin_amdgcn_exp2f(red_m[w % W][r + 8 * (w / W)] - M);
+            lsum += f[w] * red_l[w % W][r + 8 * (w / W)];
         }
         const int c0 = (kPair && r >= 8) ? 64 : 0;   // head B's channels are 64..127 of the accumulators
         float o[N];
@@ -1633,7 +1688,8 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
         for (int cc = 0; cc < N; ++cc) {
             float s = 0.f;
 #pragma unroll
-            for (int w = 0; w < W; ++w) s += f[w] * red_acc[(w * 16 + r) * kAS + c0 + N * L + cc];
+            for (int w = 0; w < H * W; ++w)
+                s += f[w] * red_acc[((w % W) * 16 + r + 8 * (w / W)) * kAS + c0 + 64 * (w / W) + N * L + cc];
             o[cc] = s;
         }
         if (in_place) {
@@ -2291,6 +2347,7 @@ static int launch_waves(const DecodeParams& p) {
         case kTq4: return Fmt<kTq4>::kWaves;
         case kFp4d64: return Fmt<kFp4d64>::kWaves;
         case kFp4d64x2: return Fmt<kFp4d64x2>::kWaves;
+        case kFp4d64p2: return Fmt<kFp4d64p2>::kWaves;
         case kFp4d256: return Fmt<kFp4d256>::kWaves;
         default: return eight_waves(p) ? 8 : Fmt<kFp4>::kWaves;
     }
@@ -2329,7 +2386,7 @@ template <int F, bool PROBE = false>
 static hipError_t launch_partials(const DecodeParams& p, hipStream_t stream) {
     constexpr int W = Fmt<F>::kWaves;
     static_assert(occupancy<F, kRingSlots, W>() == Fmt<F>::kOccupancy, "the LDS footprint lowers the occupancy");
-    if constexpr (head_dim_of<F>() == 128 && F != kFp4d64x2) {
+    if constexpr (head_dim_of<F>() == 128) {
         if (choose_wave_parts(p)) {
             if constexpr (F == kFp4 || F == kFp8) {
                 if (launch_waves(p) == 8) return launch_wave_grid<F, PROBE, 8>(p, stream);
@@ -2359,6 +2416,7 @@ hipError_t launch_gather_probe(const DecodeParams& p, uint32_t* sink, hipStream_
     pp.probe_sink = sink;
     if (p.kv_fmt == kFp4d64) return launch_partials<kFp4d64, true>(pp, stream);
     if (p.kv_fmt == kFp4d64x2) return launch_partials<kFp4d64x2, true>(pp, stream);
+    if (p.kv_fmt == kFp4d64p2) return launch_partials<kFp4d64p2, true>(pp, stream);
     if (p.kv_fmt == kFp4d256) return launch_partials<kFp4d256, true>(pp, stream);
     if (p.kv_fmt == kFp4) return launch_partials<kFp4, true>(pp, stream);
     return hipErrorInvalidValue;
@@ -2370,6 +2428,7 @@ hipError_t launch_decode_partials(const DecodeParams& p, hipStream_t stream) {
     if (p.kv_fmt == kTq4) return launch_partials<kTq4>(p, stream);
     if (p.kv_fmt == kFp4d64) return launch_partials<kFp4d64>(p, stream);
     if (p.kv_fmt == kFp4d64x2) return launch_partials<kFp4d64x2>(p, stream);
+    if (p.kv_fmt == kFp4d64p2) return launch_partials<kFp4d64p2>(p, stream);
     if (p.kv_fmt == kFp4d256) return launch_partials<kFp4d256>(p, stream);
     return launch_partials<kFp4>(p, stream);
 }

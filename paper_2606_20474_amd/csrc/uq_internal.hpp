@@ -13,7 +13,11 @@ namespace uq {
 // kFp4d64 / kFp4d256: the FP4 cache at head sizes 64 and 256 (kFp4 is 128).
 // kFp4d64x2: head size 64 with two KV heads per block, staged and computed as
 // one 128-channel head (group size at most 8, an even number of KV heads).
-enum KvFmt : int32_t { kFp4 = 0, kFp8 = 1, kBf16 = 2, kTq4 = 3, kFp4d64 = 4, kFp4d256 = 5, kFp4d64x2 = 6 };
+// kFp4d64p2: the same for an odd number of KV heads, two page pairs of one
+// head in place of the two heads.
+enum KvFmt : int32_t {
+    kFp4 = 0, kFp8 = 1, kBf16 = 2, kTq4 = 3, kFp4d64 = 4, kFp4d256 = 5, kFp4d64x2 = 6, kFp4d64p2 = 7
+};
 
 // Tables of the Ultra-TQ key codebook, built on the host from the 16 levels
 // rounded to BF16: the encoder's midpoints (c_j + c_{j+1}) / 2, exact in

@@ -303,28 +303,107 @@ __global__ void __launch_bounds__(256) quantize_kv_kernel(QuantizeParams p) {
     }
 }
 
+// Value of lane J of this lane's quad.
+template <int J>
+__device__ __forceinline__ float quad_lane(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), J * 0x55, 0xF, 0xF, true));
+}
+
+// The squared error of one 32-channel group's 8 channels in this lane, scale
+// sc: the cache encoder itself (pow2: scale operand sc = 2^E, decoded by the
+// same scale), or the nearest E2M1 level of fl32(x / sc), times sc.
+template <bool POW2>
+__device__ __forceinline__ float group_error(const float (&x)[8], float sc, float err) {
+    if constexpr (POW2) {
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) {
+            const uint32_t w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, x[i], x[i + 1], sc, 0);
+            const v2f d = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, sc, 0);
+            const float e0 = x[i] - d[0], e1 = x[i + 1] - d[1];
+            err = __builtin_fmaf(e0, e0, err);
+            err = __builtin_fmaf(e1, e1, err);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) {
+            const float t0 = x[i] / sc, t1 = x[i + 1] / sc;
+            const uint32_t w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, t0, t1, 1.0f, 0);
+            const v2f d = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, 1.0f, 0);
+            const float e0 = x[i] - d[0] * sc, e1 = x[i + 1] - d[1] * sc;
+            err = __builtin_fmaf(e0, e0, err);
+            err = __builtin_fmaf(e1, e1, err);
+        }
+    }
+    return err;
+}
+
+constexpr int kErrorWaves = 16;
+
+// The errors of constants c0 .. c0 + CG - 1 over the wave's 16 rows, added to
+// acc[c0 ..].  mq: the maximum of the group lane & 3 of the lane's row, so a
+// quad computes its row's four scales in one pass and hands them round by DPP.
+// The CG (1 or 2) sums are reduced together: in the first step each half of
+// the wave keeps one of two, and one LDS addition serves both.  (Four or eight
+// together cost registers and with them waves: 127 and 152 us for 46 constants
+// at 131072 rows against 116 with two and 120 with one.)
+template <bool POW2, int CG>
+__device__ __forceinline__ void error_constants(const float (&x)[4][8], float mq, const ErrorParams& p, int c0,
+                                                int lane, double* acc) {
+    float err[CG];
+#pragma unroll
+    for (int u = 0; u < CG; ++u) {
+        const float c = p.c_values[c0 + u];
+        // an all-zero group decodes exactly with any scale
+        const float sq = POW2 ? __builtin_ldexpf(1.0f, int(ue8m0_byte(mq, c)) - 127) : mq > 0.0f ? c * mq : 1.0f;
+        float e = group_error<POW2>(x[0], quad_lane<0>(sq), 0.0f);
+        e = group_error<POW2>(x[1], quad_lane<1>(sq), e);
+        e = group_error<POW2>(x[2], quad_lane<2>(sq), e);
+        err[u] = group_error<POW2>(x[3], quad_lane<3>(sq), e);
+    }
+    int ci = c0, s = 32;
+#pragma unroll
+    for (int w = CG / 2; w >= 1; w >>= 1, s >>= 1) {
+        const bool upper = (lane & s) != 0;   // keeps constants w .. 2 w - 1
+#pragma unroll
+        for (int i = 0; i < w; ++i) {
+            const float keep = upper ? err[i + w] : err[i];
+            const float give = upper ? err[i] : err[i + w];
+            err[i] = keep + __shfl_xor(give, s);
+        }
+        ci += upper ? w : 0;
+    }
+#pragma unroll
+    for (; s >= 1; s >>= 1) err[0] += __shfl_xor(err[0], s);
+    if ((lane & (64 / CG - 1)) == 0) acc[ci] += double(err[0]);
+}
+
 // Round-trip error of the FP4 encoder for a list of constants c, the
 // one-dimensional fit of section "Constant-Optimized Scaling": per row
 // (rotated like K when `rotate`), per 32-channel group with maximum m, the
 // codes of x / s are decoded back to code * s and the squared error summed,
 // for the deployed scale s = 2^round(log2(c m)) (UE8M0, pow2) or the
-// continuous s = c m.  One quad per row as in quantize_kv_kernel, 64 rows
-// per tile, tiles strided over the grid.  Each wave folds its per-tile sums
-// into its own fp64 LDS slots; at the end the block adds its totals to
-// `sums` with one fp64 atomic per value.
-template <int DT>
-__global__ void __launch_bounds__(256) quantize_error_kernel(ErrorParams p) {
-    __shared__ double acc[4][kMaxErrorConstants];
-    __shared__ double energy[4];
-    for (int i = threadIdx.x; i < 4 * kMaxErrorConstants; i += 256) (&acc[0][0])[i] = 0.0;
-    if (threadIdx.x < 4) energy[threadIdx.x] = 0.0;
+// continuous s = c m.  One quad per row as in quantize_kv_kernel: units of 16
+// rows per wave, dealt out to the blocks first, then to a block's waves.  Each
+// wave folds its per-unit sums into its own fp64 LDS slots; at the end a block
+// adds its totals to `sums` with one fp64 atomic per value.
+// Bound by the conversions' issue (an encode and a decode per pair of values
+// and constant; about 2 us per constant at 131072 rows).  The atomics of all
+// blocks meet on the same addresses, about 25 ns apiece: 2048 blocks of 4 waves
+// spent 51 us in them (one constant, 131072 rows: 58 us, now 24), so the grid is
+// two blocks of 16 waves per CU, which fill it.
+template <int DT, bool POW2>
+__global__ void __launch_bounds__(64 * kErrorWaves) __attribute__((amdgpu_waves_per_eu(8, 8))) quantize_error_kernel(ErrorParams p) {
+    __shared__ double acc[kErrorWaves][kMaxErrorConstants];
+    __shared__ double energy[kErrorWaves];
+    for (int i = threadIdx.x; i < kErrorWaves * kMaxErrorConstants; i += 64 * kErrorWaves) (&acc[0][0])[i] = 0.0;
+    if (threadIdx.x < kErrorWaves) energy[threadIdx.x] = 0.0;
     __syncthreads();
     const int L = threadIdx.x & 3;
+    const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    const bool lead = (threadIdx.x & 63) == 0;
-    const int64_t tiles = (p.rows + 63) / 64;
-    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-        const int64_t row = tile * 64 + (threadIdx.x >> 2);
+    const int64_t units = (p.rows + 15) / 16;
+    for (int64_t unit = blockIdx.x + int64_t(wave) * gridDim.x; unit < units; unit += int64_t(kErrorWaves) * gridDim.x) {
+        const int64_t row = unit * 16 + (lane >> 2);
         float x[4][8];
 #pragma unroll
         for (int j = 0; j < 4; ++j)
@@ -335,63 +414,38 @@ __global__ void __launch_bounds__(256) quantize_error_kernel(ErrorParams p) {
             for (int j = 0; j < 4; ++j) load_x8<DT>(p.x, row * p.row_stride + 32 * j + 8 * L, x[j]);
         }
         if (p.rotate) wht128_x32(x, L);   // whole quads: rows past the end rotate zeros
-        float m[4];
+        float mq = 0.0f;
         float sq = 0.0f;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            m[j] = 0.0f;
+            float m = 0.0f;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                m[j] = __builtin_fmaxf(m[j], __builtin_fabsf(x[j][i]));
+                m = __builtin_fmaxf(m, __builtin_fabsf(x[j][i]));
                 sq = __builtin_fmaf(x[j][i], x[j][i], sq);
             }
-            m[j] = __builtin_fmaxf(m[j], quad_xor<1>(m[j]));
-            m[j] = __builtin_fmaxf(m[j], quad_xor<2>(m[j]));
+            m = __builtin_fmaxf(m, quad_xor<1>(m));
+            m = __builtin_fmaxf(m, quad_xor<2>(m));
+            mq = L == j ? m : mq;
         }
 #pragma unroll
         for (int s = 1; s < 64; s <<= 1) sq += __shfl_xor(sq, s);
-        if (lead) energy[wave] += double(sq);
-        for (int ci = 0; ci < p.num_c; ++ci) {
-            const float c = p.c_values[ci];
-            float err = 0.0f;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (!(m[j] > 0.0f)) continue;   // an all-zero group decodes exactly
-                if (p.pow2) {
-                    // The cache encoder itself: scale operand 2^E, decode by the same scale.
-                    const float sc = __builtin_ldexpf(1.0f, int(ue8m0_byte(m[j], c)) - 127);
-#pragma unroll
-                    for (int i = 0; i < 8; i += 2) {
-                        const uint32_t w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, x[j][i], x[j][i + 1], sc, 0);
-                        const v2f d = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, sc, 0);
-                        const float e0 = x[j][i] - d[0], e1 = x[j][i + 1] - d[1];
-                        err = __builtin_fmaf(e0, e0, err);
-                        err = __builtin_fmaf(e1, e1, err);
-                    }
-                } else {
-                    // Continuous scale: nearest E2M1 level of fl32(x / s), times s.
-                    const float sc = c * m[j];
-#pragma unroll
-                    for (int i = 0; i < 8; i += 2) {
-                        const float t0 = x[j][i] / sc, t1 = x[j][i + 1] / sc;
-                        const uint32_t w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, t0, t1, 1.0f, 0);
-                        const v2f d = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, 1.0f, 0);
-                        const float e0 = x[j][i] - d[0] * sc, e1 = x[j][i + 1] - d[1] * sc;
-                        err = __builtin_fmaf(e0, e0, err);
-                        err = __builtin_fmaf(e1, e1, err);
-                    }
-                }
-            }
-#pragma unroll
-            for (int s = 1; s < 64; s <<= 1) err += __shfl_xor(err, s);
-            if (lead) acc[wave][ci] += double(err);
-        }
+        if (lane == 0) energy[wave] += double(sq);
+        int ci = 0;
+#pragma unroll 1
+        for (; ci + 2 <= p.num_c; ci += 2) error_constants<POW2, 2>(x, mq, p, ci, lane, acc[wave]);
+        if (ci < p.num_c) error_constants<POW2, 1>(x, mq, p, ci, lane, acc[wave]);
     }
     __syncthreads();
     if (threadIdx.x < p.num_c) {
         const int ci = threadIdx.x;
-        atomicAdd(&p.sums[2 * ci], acc[0][ci] + acc[1][ci] + acc[2][ci] + acc[3][ci]);
-        atomicAdd(&p.sums[2 * ci + 1], energy[0] + energy[1] + energy[2] + energy[3]);
+        double err = 0.0, sq = 0.0;
+        for (int w = 0; w < kErrorWaves; ++w) {
+            err += acc[w][ci];
+            sq += energy[w];
+        }
+        atomicAdd(&p.sums[2 * ci], err);
+        atomicAdd(&p.sums[2 * ci + 1], sq);
     }
 }
 
@@ -487,15 +541,23 @@ hipError_t launch_write_kv_ref(const RefWriteParams& p, int dtype, hipStream_t s
     return launch_ref<2>(p, grid, stream);
 }
 
+template <bool POW2>
+static void launch_error(const ErrorParams& p, int dtype, const dim3& grid, hipStream_t stream) {
+    const dim3 block{64u * kErrorWaves};
+    if (dtype == 0) hipLaunchKernelGGL((quantize_error_kernel<0, POW2>), grid, block, 0, stream, p);
+    else if (dtype == 1) hipLaunchKernelGGL((quantize_error_kernel<1, POW2>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((quantize_error_kernel<2, POW2>), grid, block, 0, stream, p);
+}
+
 hipError_t launch_quantize_error(const ErrorParams& p, int dtype, hipStream_t stream) {
-    const int64_t tiles = (p.rows + 63) / 64;
-    if (tiles == 0 || p.num_c == 0) return hipSuccess;
+    const int64_t units = (p.rows + 15) / 16;
+    if (units == 0 || p.num_c == 0) return hipSuccess;
     if (p.num_c > kMaxErrorConstants) return hipErrorInvalidValue;
-    // 8 blocks of 4 waves per CU over 256 CUs; each block strides over the tiles.
-    const dim3 grid{unsigned(tiles < 2048 ? tiles : 2048)}, block{256u};
-    if (dtype == 0) hipLaunchKernelGGL(quantize_error_kernel<0>, grid, block, 0, stream, p);
-    else if (dtype == 1) hipLaunchKernelGGL(quantize_error_kernel<1>, grid, block, 0, stream, p);
-    else hipLaunchKernelGGL(quantize_error_kernel<2>, grid, block, 0, stream, p);
+    // two blocks per CU, fewer where that leaves a block less than 4 units (one per SIMD)
+    const int64_t blocks = (units + 3) / 4;
+    const dim3 grid{unsigned(blocks < 2 * kNumCus ? blocks : 2 * kNumCus)};
+    if (p.pow2) launch_error<true>(p, dtype, grid, stream);
+    else launch_error<false>(p, dtype, grid, stream);
     return hipGetLastError();
 }
 

@@ -1352,8 +1352,7 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
             uint32_t wq = 0u;
             if (qvalid) {
                 wht_x<N>(qx[h], qL);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) wq |= e4m3_byte(qx[h][j]) << (8 * j);
+                wq = e4m3x4(qx[h][0], qx[h][1], qx[h][2], qx[h][3]);
             }
             const int ch = N * qL + (qr >= 8 ? 64 : 0);
             const int g = (ch & 63) >> 4;
@@ -1370,8 +1369,7 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
                 wht_x<N>(qx[h], qL);
 #pragma unroll
                 for (int i = 0; i < N / 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) wq[i] |= e4m3_byte(qx[h][4 * i + j]) << (8 * j);
+                    wq[i] = e4m3x4(qx[h][4 * i], qx[h][4 * i + 1], qx[h][4 * i + 2], qx[h][4 * i + 3]);
             }
             const int ch = N * qL;
             const int c2 = ch & 127;
@@ -1389,13 +1387,8 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
             uint32_t lo = qw[h][0], hi = qw[h][1];
             if (qvalid && p.q_dtype != 3) {
                 if constexpr (F == kFp4) wht128_x8(qx[h], qL);
-                lo = 0;
-                hi = 0;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    lo |= e4m3_byte(qx[h][i]) << (8 * i);
-                    hi |= e4m3_byte(qx[h][i + 4]) << (8 * i);
-                }
+                lo = e4m3x4(qx[h][0], qx[h][1], qx[h][2], qx[h][3]);
+                hi = e4m3x4(qx[h][4], qx[h][5], qx[h][6], qx[h][7]);
             }
             // FP8 operand of the 16x16x128 scaled MFMA: lane 16*g + n holds
             // column n, channels 16g..16g+15 in bytes 0..15 and
@@ -1643,7 +1636,9 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
     // zero accumulators, so its weight is 0) into one partial per block.
     __syncthreads();
     float* red_acc = reinterpret_cast<float*>(smem);
-    constexpr int kAS = DA + 1;   // LDS row stride (floats) of the merge buffer
+    // LDS row stride (floats) of the merge buffer: 16-byte aligned, 4 banks apart
+    // from row to row
+    constexpr int kAS = DA + 4;
     static_assert(W * 16 * kAS * 4 <= W * ring_bytes<F, S>(), "merge buffer aliases the staging rings");
     if (g4 == 0) {
         red_m[wave][n] = m_run;
@@ -1653,11 +1648,13 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
 #pragma unroll
     for (int bl = 0; bl < kAccTiles / 8; ++bl) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                // head size 64: rows of channel blocks 8..15 (g4 >= 2) do not exist
-                if (DA != 64 || g4 < 2) red_acc[(wave * 16 + n) * kAS + 128 * bl + 32 * g4 + 8 * i + j] = acc[8 * bl + j][i];
+        for (int i = 0; i < 4; ++i) {
+            // head size 64: rows of channel blocks 8..15 (g4 >= 2) do not exist
+            if (DA != 64 || g4 < 2) {
+                float4* dst = reinterpret_cast<float4*>(red_acc + (wave * 16 + n) * kAS + 128 * bl + 32 * g4 + 8 * i);
+                const v4f* a = acc + 8 * bl;
+                dst[0] = make_float4(a[0][i], a[1][i], a[2][i], a[3][i]);
+                dst[1] = make_float4(a[4][i], a[5][i], a[6][i], a[7][i]);
             }
         }
     }
@@ -1685,12 +1682,19 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
         const int c0 = (kPair && r >= 8) ? 64 : 0;   // head B's channels are 64..127 of the accumulators
         float o[N];
 #pragma unroll
-        for (int cc = 0; cc < N; ++cc) {
-            float s = 0.f;
+        for (int cc = 0; cc < N; ++cc) o[cc] = 0.f;
 #pragma unroll
-            for (int w = 0; w < H * W; ++w)
-                s += f[w] * red_acc[((w % W) * 16 + r + 8 * (w / W)) * kAS + c0 + 64 * (w / W) + N * L + cc];
-            o[cc] = s;
+        for (int w = 0; w < H * W; ++w) {
+            const float4* src = reinterpret_cast<const float4*>(
+                red_acc + ((w % W) * 16 + r + 8 * (w / W)) * kAS + c0 + 64 * (w / W) + N * L);
+#pragma unroll
+            for (int i = 0; i < N / 4; ++i) {
+                const float4 v = src[i];
+                o[4 * i] += f[w] * v.x;
+                o[4 * i + 1] += f[w] * v.y;
+                o[4 * i + 2] += f[w] * v.z;
+                o[4 * i + 3] += f[w] * v.w;
+            }
         }
         if (in_place) {
             // the whole context is in this block: finish here
@@ -1834,11 +1838,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
                 else if (p.q_dtype == 1) load_x8<1>(p.q, elem, qx);
                 else load_x8<2>(p.q, elem, qx);
                 wht128_x8(qx, qL);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    lo |= e4m3_byte(qx[i]) << (8 * i);
-                    hi |= e4m3_byte(qx[i + 4]) << (8 * i);
-                }
+                lo = e4m3x4(qx[0], qx[1], qx[2], qx[3]);
+                hi = e4m3x4(qx[4], qx[5], qx[6], qx[7]);
             }
         }
         const int ch = 8 * qL;

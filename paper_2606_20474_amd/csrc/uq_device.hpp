@@ -1,12 +1,12 @@
 // uq_device.hpp -- device-side building blocks shared by the libuq kernels
 // (gfx950 / CDNA4 only).
 //
-//  * wht128_x8        fixed 128-point Walsh-Hadamard rotation of a vector
-//                     spread over 16 lanes, 8 channels per lane (paper,
+//  * wht_x            fixed d-point Walsh-Hadamard rotation of a vector
+//                     spread over 16 lanes, d/16 channels per lane (paper,
 //                     section "Ultra-TurboQuant" and Algorithm 1).
 //  * ue8m0_exponent   E = round(log2(c*m)) from the fp32 bits (paper,
 //                     section "Constant-Optimized Scaling").
-//  * e4m3_byte        OCP e4m3fn, round to nearest even, saturating.
+//  * e4m3x4           OCP e4m3fn, round to nearest even, saturating.
 //  * load_x8, encode_token, place_token, store_token
 //                     one token's K/V from the input rows into a cache tile.
 #pragma once
@@ -41,43 +41,45 @@ template <int D> __device__ __forceinline__ float inv_sqrt_d() {
     return D == 64 ? 0.125f : D == 256 ? 0.0625f : inv_sqrt128();
 }
 
-// The rotation R = H_128 / sqrt(128) of one 128-vector held by 16
-// consecutive lanes (lane L of the 16 holds channels 8L..8L+7 in x[0..7]).
-// The butterfly runs stage widths 1, 2, 4 inside the lane and 8, 16, 32, 64
-// across lanes L^1, L^2, L^4, L^8; each stage maps the pair (i, i+h) to
-// (x_i + x_{i+h}, x_i - x_{i+h}) in fp32, and one fp32 multiply by
-// fl32(1/sqrt(128)) follows.  The quantised codes are decided from these
-// exact fp32 values, so the stage order is part of the cache format.
-__device__ __forceinline__ void wht128_x8(float (&x)[8], int L) {
-#pragma clang fp contract(off)
-#pragma unroll
-    for (int h = 1; h < 8; h <<= 1) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            if (i & h) continue;
-            float a = x[i], b = x[i + h];
-            x[i] = a + b;
-            x[i + h] = a - b;
-        }
+// Value of lane l ^ S of the 16-lane row, by DPP: quad permutes for 1 and 2, a
+// row rotation for 8, and for 4 a row shift either way (banks 0 and 2 of the
+// row take the lane 4 above, banks 1 and 3 the lane 4 below).  The whole row is
+// active.  (With ds_bpermute exchanges and a bitwise FP8 cast a block of the
+// decode kernel spent 0.6 us more before its first page arrived: a step of one
+// 1531-token sequence took 14.9 us, now 13.2, of 32 x 32k 98.8, now 97.6; the
+// 16-byte LDS accesses of the block merge are part of that.)
+template <int S>
+__device__ __forceinline__ float row_xor(float x) {
+    const int v = __builtin_bit_cast(int, x);
+    int r;
+    if constexpr (S == 1) r = __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);        // quad_perm [1,0,3,2]
+    else if constexpr (S == 2) r = __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);   // quad_perm [2,3,0,1]
+    else if constexpr (S == 4) {
+        r = __builtin_amdgcn_update_dpp(0, v, 0x104, 0xF, 0x5, false);                         // row_shl:4
+        r = __builtin_amdgcn_update_dpp(r, v, 0x114, 0xF, 0xA, false);                         // row_shr:4
+    } else {
+        static_assert(S == 8, "within a 16-lane row");
+        r = __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, false);                         // row_ror:8
     }
-#pragma unroll
-    for (int s = 1; s < 16; s <<= 1) {
-        const bool upper = (L & s) != 0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            float o = __shfl_xor(x[i], s, 16);
-            x[i] = upper ? (o - x[i]) : (x[i] + o);
-        }
-    }
-    const float r = inv_sqrt128();
-#pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = x[i] * r;
+    return __builtin_bit_cast(float, r);
 }
 
-// The same rotation for a head vector of 16 N channels spread over 16 lanes,
-// N per lane (lane L holds channels N L + i): stage widths 1 .. N/2 inside a
-// lane, then N .. 8 N across lanes, then one multiply by fl32(1/sqrt(16 N)).
-// wht_x<8> is wht128_x8.
+// One cross-lane butterfly stage: lanes without bit S of L get x + o, lanes
+// with it o - x (o: the value of lane L ^ S), one fma each (exactly that sum).
+template <int S, int N>
+__device__ __forceinline__ void row_stage(float (&x)[N], int L) {
+    const float s = (L & S) ? -1.0f : 1.0f;
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = __builtin_fmaf(s, x[i], row_xor<S>(x[i]));
+}
+
+// The rotation R = H_d / sqrt(d) of one head vector of d = 16 N channels held
+// by 16 consecutive lanes (lane L of the 16 holds channels N L .. N L + N - 1 in
+// x).  The butterfly runs stage widths 1 .. N / 2 inside the lane and N .. 8 N
+// across lanes L^1, L^2, L^4, L^8; each stage maps the pair (i, i+h) to
+// (x_i + x_{i+h}, x_i - x_{i+h}) in fp32, and one fp32 multiply by
+// fl32(1/sqrt(d)) follows.  The quantised codes are decided from these
+// exact fp32 values, so the stage order is part of the cache format.
 template <int N>
 __device__ __forceinline__ void wht_x(float (&x)[N], int L) {
 #pragma clang fp contract(off)
@@ -91,19 +93,15 @@ __device__ __forceinline__ void wht_x(float (&x)[N], int L) {
             x[i + h] = a - b;
         }
     }
-#pragma unroll
-    for (int s = 1; s < 16; s <<= 1) {
-        const bool upper = (L & s) != 0;
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            float o = __shfl_xor(x[i], s, 16);
-            x[i] = upper ? (o - x[i]) : (x[i] + o);
-        }
-    }
+    row_stage<1>(x, L);
+    row_stage<2>(x, L);
+    row_stage<4>(x, L);
+    row_stage<8>(x, L);
     const float r = inv_sqrt_d<16 * N>();
 #pragma unroll
     for (int i = 0; i < N; ++i) x[i] = x[i] * r;
 }
+__device__ __forceinline__ void wht128_x8(float (&x)[8], int L) { wht_x<8>(x, L); }
 
 // E = round(log2(fl32(c * m))), nearest integer in the log domain: the
 // significand of y = c*m is compared with sqrt(2) through its 23 fraction
@@ -145,24 +143,15 @@ __device__ __forceinline__ uint32_t ue8m0_byte(float m, float c) {
     return u < 0x800000u ? (u >= 0x5A827Au ? 1u : 0u) : b;
 }
 
-// OCP e4m3fn byte of x, round to nearest even, saturating to +-448.
-// Normal range: keep 3 fraction bits of the fp32 pattern with RNE (a carry
-// moves into the exponent by itself) and rebias 127 -> 7.  Below 2^-6 the
-// value is m * 2^-9 with m = rne(|x| * 512) in 0..8 (8 is the smallest normal).
-__device__ __forceinline__ uint32_t e4m3_byte(float x) {
-    const uint32_t u = f32_bits(x);
-    const uint32_t sign = (u >> 24) & 0x80u;
-    const uint32_t ua = u & 0x7FFFFFFFu;
-    const float a = bits_f32(ua);
-    uint32_t mag;
-    if (a < 0.015625f) {
-        mag = uint32_t(__builtin_rintf(a * 512.0f));
-    } else {
-        const uint32_t r = (ua + 0x7FFFFu + ((ua >> 20) & 1u)) >> 20;
-        mag = r - (120u << 3);
-        mag = mag > 0x7Eu ? 0x7Eu : mag;
-    }
-    return sign | mag;
+// The OCP e4m3fn bytes of four values, packed low byte first: round to nearest
+// even (subnormals included), saturating to +-448.
+__device__ __forceinline__ uint32_t e4m3x4(float a, float b, float c, float d) {
+    typedef short v2s __attribute__((ext_vector_type(2)));
+    auto sat = [](float x) { return __builtin_amdgcn_fmed3f(x, -448.0f, 448.0f); };
+    v2s w = {0, 0};
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w, sat(a), sat(b), 1.0f, false);
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w, sat(c), sat(d), 1.0f, true);
+    return __builtin_bit_cast(uint32_t, w);
 }
 
 // Eight consecutive channels starting at element `elem` as fp32 (DT: 0 f32,
@@ -218,8 +207,8 @@ __device__ __forceinline__ uint32_t quantize_x8(float (&x)[8], int L, float c, b
     float m = 0.0f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) m = __builtin_fmaxf(m, __builtin_fabsf(x[i]));
-    m = __builtin_fmaxf(m, __shfl_xor(m, 1, 16));
-    m = __builtin_fmaxf(m, __shfl_xor(m, 2, 16));
+    m = __builtin_fmaxf(m, row_xor<1>(m));
+    m = __builtin_fmaxf(m, row_xor<2>(m));
     const int E = ue8m0_exponent(m, c);
     scale_byte = uint32_t(E + 127);
     // E2M1 codes of x / 2^E by the hardware conversion (nearest level, ties
@@ -370,11 +359,11 @@ __device__ __forceinline__ TokenBits<F> encode_token(float (&xk)[8], float (&xv)
         t.k = quantize_x8(xk, lane16, c, true, t.ks);
         t.v = quantize_x8(xv, lane16, c, rotate_v, t.vs);
     } else if constexpr (F == kFp8) {
-        uint32_t kw[2] = {0u, 0u}, vw[2] = {0u, 0u};
+        uint32_t kw[2], vw[2];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            kw[i >> 2] |= e4m3_byte(xk[i] / k_scale) << (8 * (i & 3));
-            vw[i >> 2] |= e4m3_byte(xv[i] / v_scale) << (8 * (i & 3));
+        for (int i = 0; i < 2; ++i) {
+            kw[i] = e4m3x4(xk[4 * i] / k_scale, xk[4 * i + 1] / k_scale, xk[4 * i + 2] / k_scale, xk[4 * i + 3] / k_scale);
+            vw[i] = e4m3x4(xv[4 * i] / v_scale, xv[4 * i + 1] / v_scale, xv[4 * i + 2] / v_scale, xv[4 * i + 3] / v_scale);
         }
         t.k = make_uint2(kw[0], kw[1]);
         t.v = make_uint2(vw[0], vw[1]);

@@ -492,13 +492,8 @@ __global__ void __launch_bounds__(256) prepare_query_kernel(const void* q, int64
     float x[8];
     load_x8<DT>(q, row * kHeadDim + 8 * lane16, x);
     wht128_x8(x, lane16);
-    uint32_t lo = 0, hi = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        lo |= e4m3_byte(x[i]) << (8 * i);
-        hi |= e4m3_byte(x[i + 4]) << (8 * i);
-    }
-    *reinterpret_cast<uint2*>(q8 + row * kHeadDim + 8 * lane16) = make_uint2(lo, hi);
+    *reinterpret_cast<uint2*>(q8 + row * kHeadDim + 8 * lane16) =
+        make_uint2(e4m3x4(x[0], x[1], x[2], x[3]), e4m3x4(x[4], x[5], x[6], x[7]));
 }
 
 template <int NG>

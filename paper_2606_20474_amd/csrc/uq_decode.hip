@@ -12,8 +12,8 @@
 //   kBf16  a plain BF16 cache;
 //   kTq4   the Ultra-TQ codebook cache (rotated K as 4-bit indices into 16
 //          levels times a per-token norm; V as 4-bit uniform codes with a
-//          BF16 (scale, zero) per 32 channels): K is decoded in registers
-//          by byte-permute table lookups into BF16 levels, QK^T runs on
+//          BF16 (scale, zero) per 32 channels): K is decoded two indices at
+//          a time through an LDS table of BF16 level pairs, QK^T runs on
 //          BF16 matrix instructions and each score is multiplied by its
 //          token's norm; V is decoded with one fused multiply-add per
 //          element into BF16.
@@ -169,9 +169,10 @@ template <int F, int S> constexpr int ring_bytes() { return S * stage_bytes<F>()
 template <int F> constexpr int q_lds_bytes() {
     return (F == kBf16 || F == kTq4) ? 4 * 64 * 16 : (head_dim_of<F>() / 128 + (head_dim_of<F>() < 128)) * 64 * 32;
 }
+template <int F> constexpr int tq_lds_bytes() { return F == kTq4 ? 1024 : 0; }   // the Ultra-TQ pair table
 constexpr int kIdsSlot = 256;   // LDS bytes per wave for the next 64 page ids
 template <int F, int S, int W = Fmt<F>::kWaves> constexpr int block_lds_bytes() {
-    return W * (ring_bytes<F, S>() + kIdsSlot) + q_lds_bytes<F>() + 2 * W * 16 * 4;
+    return W * (ring_bytes<F, S>() + kIdsSlot) + q_lds_bytes<F>() + tq_lds_bytes<F>() + 2 * W * 16 * 4;
 }
 // Waves per SIMD with an S-slot ring and W waves per block: what 160 KiB of
 // LDS per CU holds, capped by the format's register-set budget.
@@ -582,34 +583,55 @@ __device__ __forceinline__ void stage_read(StageRegs<kTq4>& r, uint32_t stage_ad
 template <int F> struct QOperand { v8i q; };               // FP8 bytes, 32 per lane
 template <> struct QOperand<kBf16> { v8bf q[4]; };          // 4 k-steps x 8 BF16 per lane
 template <> struct QOperand<kFp4d256> { v8i q[2]; };        // FP8 bytes of the two 128-channel chunks
-// Ultra-TQ: the BF16 query with each k-step's 8 channels in the order
-// 0, 2, 4, 6, 1, 3, 5, 7 (the order the index decoder produces), and the
-// codebook's byte tables.
+// Ultra-TQ: the BF16 query, and the LDS address of the pair table.
 template <> struct QOperand<kTq4> {
     v8bf q[4];
-    uint32_t lut[8];
+    uint32_t table;
 };
 
-// BF16 levels of 8 K indices (nibble i of w = channel i): the byte tables
-// are looked up with v_perm (8 entries per instruction, the 4th index bit
-// picks the half), high and low bytes separately, then interleaved into
-// BF16 pairs (channels 0,2), (4,6), (1,3), (5,7).
-__device__ __forceinline__ uint4 tq_decode8(uint32_t w, const uint32_t (&lut)[8]) {
-    const uint32_t e = w & 0x0F0F0F0Fu;            // byte j: index of channel 2j
-    const uint32_t o = (w >> 4) & 0x0F0F0F0Fu;     // byte j: index of channel 2j+1
-    const uint32_t se = e & 0x07070707u, so = o & 0x07070707u;
-    const uint32_t te = ((e >> 1) & 0x04040404u) | 0x03020100u;
-    const uint32_t to = ((o >> 1) & 0x04040404u) | 0x03020100u;
-    const uint32_t he = __builtin_amdgcn_perm(__builtin_amdgcn_perm(lut[3], lut[2], se),
-                                              __builtin_amdgcn_perm(lut[1], lut[0], se), te);
-    const uint32_t le = __builtin_amdgcn_perm(__builtin_amdgcn_perm(lut[7], lut[6], se),
-                                              __builtin_amdgcn_perm(lut[5], lut[4], se), te);
-    const uint32_t ho = __builtin_amdgcn_perm(__builtin_amdgcn_perm(lut[3], lut[2], so),
-                                              __builtin_amdgcn_perm(lut[1], lut[0], so), to);
-    const uint32_t lo = __builtin_amdgcn_perm(__builtin_amdgcn_perm(lut[7], lut[6], so),
-                                              __builtin_amdgcn_perm(lut[5], lut[4], so), to);
-    return uint4{__builtin_amdgcn_perm(he, le, 0x05010400u), __builtin_amdgcn_perm(he, le, 0x07030602u),
-                 __builtin_amdgcn_perm(ho, lo, 0x05010400u), __builtin_amdgcn_perm(ho, lo, 0x07030602u)};
+// The pair table of the Ultra-TQ cache: entry b holds the BF16 levels of the
+// two K indices in byte b (low nibble = even channel in the low half), 256
+// dwords per block.  Here by byte permutes from the levels' byte tables (8 of 16
+// entries per v_perm, the 4th index bit picks the half).
+__device__ __forceinline__ uint32_t tq_pair(uint32_t b, const uint32_t (&lut)[8]) {
+    const uint32_t w = (b & 0xFu) | ((b & 0xF0u) << 4);   // byte 0: the even channel's index, byte 1: the odd one's
+    const uint32_t s = w & 0x0707u;
+    const uint32_t t = ((w >> 1) & 0x0404u) | 0x0100u;
+    const uint32_t hi = __builtin_amdgcn_perm(__builtin_amdgcn_perm(lut[3], lut[2], s),
+                                              __builtin_amdgcn_perm(lut[1], lut[0], s), t);
+    const uint32_t lo = __builtin_amdgcn_perm(__builtin_amdgcn_perm(lut[7], lut[6], s),
+                                              __builtin_amdgcn_perm(lut[5], lut[4], s), t);
+    return __builtin_amdgcn_perm(hi, lo, 0x05010400u);
+}
+
+// BF16 levels of a page's 4 dwords of K indices per lane (8 channels each, one
+// k-step): one address and one table read per two channels.  In registers the
+// same lookup takes 25 instructions per 8 channels (byte permutes on both bytes
+// of the levels), which bound the kernel: 16 sequences of 9k-20k tokens, 64/4
+// heads, 52.9 us a step, 48.8 us with the table.  The reads' wait is in the same
+// block (the compiler does not know they are in flight).
+__device__ __forceinline__ void tq_levels(const uint4& k, uint32_t table, uint4 (&v)[4]) {
+    uint32_t a[16];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t w = i == 0 ? k.x : i == 1 ? k.y : i == 2 ? k.z : k.w;
+        a[4 * i] = ((w << 2) & 0x3FCu) + table;
+        a[4 * i + 1] = ((w >> 6) & 0x3FCu) + table;
+        a[4 * i + 2] = ((w >> 14) & 0x3FCu) + table;
+        a[4 * i + 3] = ((w >> 22) & 0x3FCu) + table;
+    }
+#pragma unroll
+    for (int h = 0; h < 16; h += 8)
+        asm volatile(
+            "ds_read_b32 %0, %0\n\tds_read_b32 %1, %1\n\tds_read_b32 %2, %2\n\tds_read_b32 %3, %3\n\t"
+            "ds_read_b32 %4, %4\n\tds_read_b32 %5, %5\n\tds_read_b32 %6, %6\n\tds_read_b32 %7, %7\n\t"
+            "s_waitcnt lgkmcnt(0)"
+            : "+v"(a[h]), "+v"(a[h + 1]), "+v"(a[h + 2]), "+v"(a[h + 3]), "+v"(a[h + 4]), "+v"(a[h + 5]), "+v"(a[h + 6]),
+              "+v"(a[h + 7])
+            :
+            : "memory");
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = uint4{a[4 * i], a[4 * i + 1], a[4 * i + 2], a[4 * i + 3]};
 }
 
 // S^T[token][query head] of one page: rows = the page's 16 tokens (lane's
@@ -650,10 +672,11 @@ __device__ __forceinline__ uint32_t dword(const uint4& v, int i) { return i == 0
 // Ultra-TQ: <q, c[idx]> on the BF16 levels, then times the token's norm.
 __device__ __forceinline__ v4f qk_page(const StageRegs<kTq4>& r, int pg, const QOperand<kTq4>& q) {
     v4f s = {0.f, 0.f, 0.f, 0.f};
+    uint4 k[4];
+    tq_levels(r.k[pg], q.table, k);
 #pragma unroll
     for (int st = 0; st < 4; ++st)
-        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, tq_decode8(dword(r.k[pg], st), q.lut)),
-                                                    q.q[st], s, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, k[st]), q.q[st], s, 0, 0, 0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) s[i] *= bits_f32(dword(r.kn[pg], i));
     return s;
@@ -725,23 +748,41 @@ __device__ __forceinline__ void pv_pair_fp4(const uint4& v0, const uint4& v1, co
     acc_o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Vo, Plo, acc_o, 0, 0, 0);
 }
 
+// The even channels' V codes of a stage, one per byte.  The empty asm keeps the
+// masked bytes as they are, so that each becomes a float in one
+// v_cvt_f32_ubyteN (seen through, the compiler extracts every nibble by itself
+// first); the odd channels' codes are extracted one by one (keeping them too
+// takes more registers than 3 waves per SIMD have).
+struct TqCodes {
+    uint32_t e[2][4];
+};
+__device__ __forceinline__ TqCodes tq_codes(const StageRegs<kTq4>& r) {
+    TqCodes c;
+#pragma unroll
+    for (int pg = 0; pg < 2; ++pg)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            c.e[pg][t] = dword(r.v[pg], t) & 0x0F0F0F0Fu;
+            asm volatile("" : "+v"(c.e[pg][t]));
+        }
+    return c;
+}
+
 // Ultra-TQ PV for channel pair C: each V value is bf16(fma(scale, code,
 // zero)) of its token's group, packed two tokens per register in the k-slot
 // order of P.
 template <int C>
-__device__ __forceinline__ void pv_pair(const StageRegs<kTq4>& r, const float (&)[2][4], const v8bf& Phi,
-                                        const v8bf& Plo, v4f& acc_e, v4f& acc_o) {
+__device__ __forceinline__ void pv_pair_tq4(const StageRegs<kTq4>& r, const TqCodes& code, const v8bf& Phi,
+                                            const v8bf& Plo, v4f& acc_e, v4f& acc_o) {
     float ve[2][4], vo[2][4];
 #pragma unroll
     for (int pg = 0; pg < 2; ++pg) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            const uint32_t w = dword(r.v[pg], t);
-            const uint32_t e = w & 0x0F0F0F0Fu, o = (w >> 4) & 0x0F0F0F0Fu;
             const uint32_t m = dword(r.vm[pg], t);
             const float s = bits_f32(m << 16), z = bits_f32(m & 0xFFFF0000u);
-            ve[pg][t] = __builtin_fmaf(s, float((e >> (8 * C)) & 0xFFu), z);
-            vo[pg][t] = __builtin_fmaf(s, float((o >> (8 * C)) & 0xFFu), z);
+            ve[pg][t] = __builtin_fmaf(s, float((code.e[pg][t] >> (8 * C)) & 0xFFu), z);
+            vo[pg][t] = __builtin_fmaf(s, float((dword(r.v[pg], t) >> (8 * C + 4)) & 0xFu), z);
         }
     }
     const uint4 ae = {pack_bf16x2(ve[0][0], ve[0][1]), pack_bf16x2(ve[0][2], ve[0][3]), pack_bf16x2(ve[1][0], ve[1][1]),
@@ -1334,15 +1375,9 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
             // channels 8*qL..+7 are k-step qL/4, lane (qL%4)*16 + qr, 16 bytes
             uint4 w = {0u, 0u, 0u, 0u};
             if (qvalid) {
-                if constexpr (F == kTq4) {
-                    // rotated like the keys, channels in the decoder's order
-                    wht128_x8(qx[h], qL);
-                    w = uint4{pack_bf16x2(qx[h][0], qx[h][2]), pack_bf16x2(qx[h][4], qx[h][6]),
-                              pack_bf16x2(qx[h][1], qx[h][3]), pack_bf16x2(qx[h][5], qx[h][7])};
-                } else {
-                    w = uint4{pack_bf16x2(qx[h][0], qx[h][1]), pack_bf16x2(qx[h][2], qx[h][3]),
-                              pack_bf16x2(qx[h][4], qx[h][5]), pack_bf16x2(qx[h][6], qx[h][7])};
-                }
+                if constexpr (F == kTq4) wht128_x8(qx[h], qL);   // rotated like the keys
+                w = uint4{pack_bf16x2(qx[h][0], qx[h][1]), pack_bf16x2(qx[h][2], qx[h][3]),
+                          pack_bf16x2(qx[h][4], qx[h][5]), pack_bf16x2(qx[h][6], qx[h][7])};
             }
             *reinterpret_cast<uint4*>(q_lds + ((qL >> 2) * 64 + (qL & 3) * 16 + qr) * 16) = w;
         } else if constexpr (kPair || kTwo) {
@@ -1399,16 +1434,21 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
             *reinterpret_cast<uint2*>(q_lds + (g * 16 + qr) * 32 + e0) = make_uint2(lo, hi);
         }
     }
+    __shared__ uint32_t tq_table[tq_lds_bytes<F>() / 4 + 1];
+    if constexpr (F == kTq4) {
+        static_assert(kThreads == 256, "one table entry per thread");
+        uint32_t lut[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) lut[j] = p.tq.lut[j];
+        tq_table[tid] = tq_pair(uint32_t(tid), lut);
+    }
     if constexpr (!PROBE) __syncthreads();
     QOperand<regs_fmt<F>()> qop;
     if constexpr (F == kBf16 || F == kTq4) {
 #pragma unroll
         for (int st = 0; st < 4; ++st)
             qop.q[st] = __builtin_bit_cast(v8bf, *reinterpret_cast<const uint4*>(q_lds + (st * 64 + lane) * 16));
-        if constexpr (F == kTq4) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) qop.lut[j] = p.tq.lut[j];
-        }
+        if constexpr (F == kTq4) qop.table = uint32_t(reinterpret_cast<uintptr_t>((lds_ptr_t)tq_table));
     } else if constexpr (F == kFp4d256) {
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
@@ -1607,6 +1647,12 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
                 pv_pair_fp4<2>(v0, v1, sc, Phi, Plo, acc[8 * bl + 4], acc[8 * bl + 5]);
                 pv_pair_fp4<3>(v0, v1, sc, Phi, Plo, acc[8 * bl + 6], acc[8 * bl + 7]);
             }
+        } else if constexpr (F == kTq4) {
+            const TqCodes code = tq_codes(c);
+            pv_pair_tq4<0>(c, code, Phi, Plo, acc[0], acc[1]);
+            pv_pair_tq4<1>(c, code, Phi, Plo, acc[2], acc[3]);
+            pv_pair_tq4<2>(c, code, Phi, Plo, acc[4], acc[5]);
+            pv_pair_tq4<3>(c, code, Phi, Plo, acc[6], acc[7]);
         } else {
             float sc[2][4];
             sc[0][0] = byte_scale0(vs0, k23);

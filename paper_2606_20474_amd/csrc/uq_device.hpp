@@ -294,39 +294,76 @@ __device__ __forceinline__ float exact_norm128(const float (&x)[8], int lane16) 
     return f;
 }
 
+// exact_norm128 with its long form only where it can matter: the plain fp64 sum
+// of the squares and its root are within 2^-48 of the exact norm, so when the
+// values 2^-44 below and above round to the same float, that is the answer.
+__device__ __forceinline__ float norm128(const float (&x)[8], int lane16) {
+#pragma clang fp contract(off)
+    double h = 0.0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) h = __builtin_fma(double(x[i]), double(x[i]), h);
+#pragma unroll
+    for (int s = 1; s < 16; s <<= 1) h += __shfl_xor(h, s, 16);   // the same bits in every lane
+    const double r = __builtin_sqrt(h);
+    const float lo = float(r * (1.0 - 0x1p-44)), hi = float(r * (1.0 + 0x1p-44));
+    return lo == hi ? lo : exact_norm128(x, lane16);
+}
+
+// Index of the level nearest to x / n, ties to the lower one: the number of
+// midpoints m_j (exact doubles) with x > m_j n, each decided by the sign of
+// fma(-m_j, n, x) in fp64, which is the sign of the exact x - m_j n.  The
+// search halves the levels with fp32 midpoints; its differences are within
+// 2^-22 (|x| + |m_j n|) of the exact ones, so their signs hold unless one on the
+// search path (the two midpoints next to x are always on it) is within 2^-20 |x|
+// of zero: then all 15 are decided in fp64.
+__device__ __forceinline__ uint32_t tq4_index(float x, float n, const float (&mid)[15], const TqTables& tq) {
+    float near = __builtin_inff();
+    auto above = [&](float m) {
+        const float d = __builtin_fmaf(-m, n, x);
+        near = __builtin_fminf(near, __builtin_fabsf(d));
+        return d > 0.0f;
+    };
+    const bool b3 = above(mid[7]);
+    const bool b2 = above(b3 ? mid[11] : mid[3]);
+    const float q0 = b2 ? mid[5] : mid[1], q1 = b2 ? mid[13] : mid[9];
+    const bool b1 = above(b3 ? q1 : q0);
+    const float e0 = b1 ? mid[2] : mid[0], e1 = b1 ? mid[6] : mid[4], e2 = b1 ? mid[10] : mid[8], e3 = b1 ? mid[14] : mid[12];
+    const float f0 = b2 ? e1 : e0, f1 = b2 ? e3 : e2;
+    const bool b0 = above(b3 ? f1 : f0);
+    uint32_t idx = (b3 ? 8u : 0u) + (b2 ? 4u : 0u) + (b1 ? 2u : 0u) + (b0 ? 1u : 0u);
+    if (!(near > 0x1p-20f * __builtin_fabsf(x))) {
+        idx = 0u;
+#pragma unroll 1
+        for (int j = 0; j < 15; ++j) idx += __builtin_fma(-tq.mid[j], double(n), double(x)) > 0.0 ? 1u : 0u;
+    }
+    return idx;
+}
+
 // Ultra-TQ encoding of the 8 channels this lane holds (all 16 lanes of the
-// vector take part).  K: rotated; n = the l2 norm rounded once to fp32
-// (exact_norm128); index = that of the level nearest to x / n, ties to the
-// lower one: the number of midpoints m_j (exact doubles) with x > m_j n,
-// each decided by the sign of fma(-m_j, n, x) in fp64, which is the sign of
-// the exact x - m_j n (index 0 when n = 0).  V: per 32-channel group (4
+// vector take part).  K: rotated; n = the l2 norm rounded once to fp32; the
+// index of the nearest level (index 0 when n = 0).  V: per 32-channel group (4
 // lanes) zero = bf16(min), scale = bf16(max(max - zero, 0) / 15), code =
 // clamp(rint((x - zero) / scale), 0, 15).
 __device__ __forceinline__ void tq4_encode(float (&xk)[8], const float (&xv)[8], int lane16, const TqTables& tq,
                                            TokenBits<kTq4>& t) {
     wht128_x8(xk, lane16);
-    const float n = exact_norm128(xk, lane16);
-    const double nd = n;
+    const float n = norm128(xk, lane16);
+    float mid[15];
+#pragma unroll
+    for (int j = 0; j < 15; ++j) mid[j] = float(tq.mid[j]);
     uint32_t wk = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        uint32_t idx = 0;
-        if (n > 0.0f) {
-#pragma unroll
-            for (int j = 0; j < 15; ++j) idx += __builtin_fma(-tq.mid[j], nd, double(xk[i])) > 0.0 ? 1u : 0u;
-        }
-        wk |= idx << (4 * i);
-    }
+    for (int i = 0; i < 8; ++i) wk |= (n > 0.0f ? tq4_index(xk[i], n, mid, tq) : 0u) << (4 * i);
     float mn = xv[0], mx = xv[0];
 #pragma unroll
     for (int i = 1; i < 8; ++i) {
         mn = __builtin_fminf(mn, xv[i]);
         mx = __builtin_fmaxf(mx, xv[i]);
     }
-    mn = __builtin_fminf(mn, __shfl_xor(mn, 1, 16));
-    mn = __builtin_fminf(mn, __shfl_xor(mn, 2, 16));
-    mx = __builtin_fmaxf(mx, __shfl_xor(mx, 1, 16));
-    mx = __builtin_fmaxf(mx, __shfl_xor(mx, 2, 16));
+    mn = __builtin_fminf(mn, row_xor<1>(mn));
+    mn = __builtin_fminf(mn, row_xor<2>(mn));
+    mx = __builtin_fmaxf(mx, row_xor<1>(mx));
+    mx = __builtin_fmaxf(mx, row_xor<2>(mx));
     const float z = bf16_round(mn);
     float d = mx - z;
     if (!(d > 0.0f)) d = 0.0f;

@@ -185,8 +185,8 @@ int32_t uq_default_partition(const uq_cache_desc *desc, int32_t batch, int32_t n
  * wave per partition, a block taking W consecutive partitions of one
  * sequence and kv head and reducing their partials into one before the
  * merge.  With the default partition (0, or its value), more than one of
- * them, no shared prefix and up to 256 sequences, the block grid instead
- * shares its rows among the sequences by their lengths, read on the device:
+ * them, no shared prefix and up to 256 sequences, the launch instead takes a
+ * block grid that shares its rows among the sequences by their lengths, read on the device:
  * the kernels cut every context into equal partitions of the shortest length
  * for which the rows suffice, so that a ragged batch, or one far below
  * max_context, still fills the GPU.  The result does not depend on the grid

@@ -867,7 +867,7 @@ __device__ __forceinline__ uint32_t fold_words(const R& r) {
 
 // ---------------------------------------------------------------------------
 // The balanced split of a batch's contexts (calls without a shared prefix that
-// leave the partition to the library, on the block grid).  The launch has
+// leave the partition to the library; always the block grid).  The launch has
 // plan_rows rows per kv head, each one block and one partial row of the
 // workspace; how the sequences share them is decided on the device from the
 // context lengths: the shortest partition P (a multiple of kPlanUnit) with
@@ -876,8 +876,9 @@ __device__ __forceinline__ uint32_t fold_words(const R& r) {
 // the host's bound of the lengths, the rows of short contexts went unused and
 // the longest partitions ran alone at the end.  Step before / after, one
 // MI355X: 12 sequences of 0.3k-55k tokens under a 64k bound (48/8 heads)
-// 71 / 44 us; 64 sequences of 0.3k-64k (64/8 heads) 203 / 134 us; equal lengths
-// unchanged (32 x 32k, 64/4 heads: 100 us).
+// 71 / 44 us; 64 sequences of 0.3k-64k (64/8 heads) 203 / 134 us; 128 of 4k-128k
+// (48/8 heads, the wave grid before) 871 / 682 us; equal lengths unchanged (32 x
+// 32k, 64/4 heads: 100 us).
 //
 // Every wave computes the plan for itself (lane l holds sequences l * per ..
 // l * per + per - 1, per <= 4): the sums and the scan are DPP.  The search
@@ -2386,7 +2387,7 @@ static bool wave_grid_with(const DecodeParams& p, int W) {
     const int64_t blocks = int64_t(p.batch) * p.num_kv_heads * ((p.num_partitions + W - 1) / W);
     return blocks >= 8 * kNumCus;
 }
-static bool eight_waves(const DecodeParams& p) { return p.num_partitions >= 16 && wave_grid_with(p, 8); }
+static bool eight_waves(const DecodeParams& p) { return p.plan_rows == 0 && p.num_partitions >= 16 && wave_grid_with(p, 8); }
 static int launch_waves(const DecodeParams& p) {
     switch (p.kv_fmt) {
         case kFp8: return eight_waves(p) ? 8 : Fmt<kFp8>::kWaves;
@@ -2404,7 +2405,9 @@ static int launch_waves(const DecodeParams& p) {
 // several (at least 8 per CU), head size 128, no cascade; else one block per
 // partition.  The merge launch makes the same choice from the same
 // parameters.
-static bool choose_wave_parts(const DecodeParams& p) { return wave_grid_with(p, launch_waves(p)); }
+// A balanced split (the default partition of up to 256 sequences) takes the
+// block grid.
+static bool choose_wave_parts(const DecodeParams& p) { return p.plan_rows == 0 && wave_grid_with(p, launch_waves(p)); }
 
 // Two ring slots per wave: a 4-slot ring (twice the copies in flight, half
 // the blocks per CU) measured no faster on 32k contexts and slower on 16k,
@@ -2417,7 +2420,6 @@ static hipError_t launch_wave_grid(const DecodeParams& p, hipStream_t stream) {
     static_assert(occupancy<F, kRingSlots, W>() == Fmt<F>::kOccupancy, "the LDS footprint lowers the occupancy");
     DecodeParams pw = p;
     pw.wave_parts = W;
-    pw.plan_rows = 0;
     const dim3 grid{unsigned(int64_t((p.num_partitions + W - 1) / W) * p.num_kv_heads * p.batch)};
     launch_kernel(decode_kernel<F, kRingSlots, true, PROBE, W>, grid, dim3(64 * W), stream, pw);
     return hipGetLastError();
@@ -2499,7 +2501,6 @@ hipError_t launch_decode_merge(const DecodeParams& p, hipStream_t stream) {
     if (p.num_partitions <= 1 && p.prefix_pages == nullptr) return hipSuccess;   // every sequence was finished in place
     DecodeParams pm = p;
     pm.wave_parts = choose_wave_parts(p) ? launch_waves(p) : 0;
-    if (pm.wave_parts != 0) pm.plan_rows = 0;
     if (p.head_dim == 64) return launch_merge<64>(pm, stream);
     if (p.head_dim == 256) return launch_merge<256>(pm, stream);
     return launch_merge<128>(pm, stream);

@@ -6,7 +6,8 @@ A call with partition 0 cuts every context by the plan the device makes from
 the lengths; the same call with an explicit partition that is not the
 default keeps one partition length per launch, the path the other tests hold
 to the oracle.  Batches of 1, 64 (one length per planner lane), 65 and 256
-(up to four), and 257 (fixed partitions again); lengths at the edges of the
+(up to four), 257 (fixed partitions again), and of 1040 and 2048 (sequence, KV
+head) pairs, which would fill the wave grid; lengths at the edges of the
 plan's 128-token unit, empty contexts, all lengths equal, one long context
 among short ones; a bound of the lengths far above them; every cache format
 and head size.  Both paths round P to two BF16 terms, |error| <= 2^-16 |P|, so
@@ -57,6 +58,8 @@ def lens(kind, batch, top):
     (130, 6, 1, "one-long", 9000, 0, "fp4", 128),
     (256, 4, 2, "edges", 4099, 0, "fp4", 128),
     (257, 4, 2, "edges", 4099, 0, "fp4", 128),
+    (130, 8, 8, "edges", 2100, 65536, "fp4", 128),
+    (256, 8, 8, "one-long", 17000, 131072, "fp4", 128),
     (12, 16, 2, "edges", 5000, 0, "fp8", 128),
     (12, 16, 2, "edges", 5000, 0, "bf16", 128),
     (12, 16, 2, "edges", 5000, 0, "tq4", 128),

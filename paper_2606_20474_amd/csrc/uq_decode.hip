@@ -2333,8 +2333,9 @@ __global__ void __launch_bounds__(1024) cascade_rows_kernel(DecodeParams p) {
         return end - start;
     };
     // class 0: a whole partition; kClasses - 1: the fewest tokens
+    const float per_token = float(kClasses - 1) / float(P);
     auto class_of = [&](int t) {
-        const int c = int(int64_t(P - t) * (kClasses - 1) / P);
+        const int c = int(float(P - t) * per_token);
         return c < 0 ? 0 : (c > kClasses - 1 ? kClasses - 1 : c);
     };
     for (int r = tid; r < R; r += kClasses) {
@@ -2343,16 +2344,16 @@ __global__ void __launch_bounds__(1024) cascade_rows_kernel(DecodeParams p) {
         if (t >= 0) atomicAdd(&hist[class_of(t)], 1);
     }
     __syncthreads();
-    // prefix sum of the class counts (Hillis-Steele over the 1024 threads)
+    // prefix sum of the class counts: within each wave, then the waves' totals
+    // (one barrier; a Hillis-Steele scan through LDS took twenty, and 1.1 us of the
+    // kernel: 4.2 against 3.1 us at its fastest, MiniMax-like batch)
+    __shared__ int wave_total[kClasses / 64];
     const int count = hist[tid];
-    int v = count;
-    for (int d = 1; d < kClasses; d <<= 1) {
-        __syncthreads();
-        hist[tid] = v;
-        __syncthreads();
-        if (tid >= d) v += hist[tid - d];
-    }
+    int v = wave_scan(count);
+    if ((tid & 63) == 63) wave_total[tid >> 6] = v;
     __syncthreads();
+    const int before = wave_scan((tid & 63) < (tid >> 6) ? wave_total[tid & 15] : 0);
+    v += __builtin_amdgcn_readlane(before, 63);
     if (tid == kClasses - 1) total = v;
     hist[tid] = v - count;   // the first list position of the class
     __syncthreads();

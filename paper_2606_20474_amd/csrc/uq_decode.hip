@@ -1530,6 +1530,20 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
             continue;
         }
 
+        const int it = woff + ws * k;
+        if constexpr (kTwo) {
+            // A row of the product holds a token of pair A (k-blocks 0, 1) and one of
+            // pair B (lanes 32..63: k-blocks 2, 3).  A token past the end may never
+            // have been written, and a scale byte of 255 is a NaN, which the zero half
+            // of the query does not remove: pair B's then take a finite scale, so that
+            // they leave pair A's scores alone.  (Pair B lies after pair A.)
+            if (start + kSpan * it + kSpan > end) {
+#pragma unroll
+                for (int pg = 0; pg < 2; ++pg)
+                    if (lane >= 32 && start + kSpan * it + 32 + 16 * pg + (lane & 15) >= end) c.ks[pg] = 127u;
+            }
+        }
+
         // ---- QK^T: raw scores (the softmax scale is applied in the exponent)
         const v4f s0 = qk_page(c, 0, qop);
         const v4f s1 = qk_page(c, 1, qop);
@@ -1544,7 +1558,6 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
             vs0 = c.vs[0];
             vs1 = c.vs[1];
         }
-        const int it = woff + ws * k;
         // token of x[0]; x[4] is tok0 + 16 (kTwo: columns 8..15 and channel
         // blocks 8..15 belong to the second page pair)
         const int tok0 = start + kSpan * it + 4 * g4 + (kTwo && n >= 8 ? 32 : 0);

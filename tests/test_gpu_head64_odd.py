@@ -29,3 +29,22 @@ def test_decode_edges(uq, hq, hkv, partition, rotate_v):  # noqa: F811
     ref = oracle.decode_attention(wl.q.numpy(), pools, wl.page_table, wl.context_lens, hkv, 1 / math.sqrt(64), rotate_v)
     assert np.all(out[-1] == 0)
     check(out, ref, f"{hq}/{hkv} p={partition}")
+
+
+@pytest.mark.parametrize("hq,hkv", [(8, 1), (5, 1), (3, 3), (8, 2), (12, 1)])
+@pytest.mark.parametrize("partition", [0, 16, 48, 64, 80])
+def test_unwritten_tokens(uq, hq, hkv, partition):  # noqa: F811
+    """Slots no token was written to hold 0xFF bytes (a scale byte of 255 is a
+    NaN), the whole of physical page 0 among them, which stands in for the pages
+    past the end: they do not reach the output.  Also the blocks of two KV heads
+    and of one (group size above 8)."""
+    dev = torch.device("cuda:0")
+    wl = workloads.custom(len(CTX), hq, hkv, CTX, seed=65, paging="random", head_dim=64)
+    wl.page_table = wl.page_table + 1   # page 0 belongs to no sequence
+    wl.num_pages += 1
+    print(f"head size 64, {hq}/{hkv} heads, partition {partition}, unwritten slots 0xFF", flush=True)
+    desc, codes, scales, pools = both_caches(uq, wl, dev, fill=0xFF)
+    out = decode(uq, wl, desc, codes, scales, dev, partition)
+    ref = oracle.decode_attention(wl.q.numpy(), pools, wl.page_table, wl.context_lens, hkv, 1 / math.sqrt(64), True)
+    assert np.all(out[-1] == 0)
+    check(out, ref, f"{hq}/{hkv} p={partition}")

@@ -228,10 +228,9 @@ __device__ __forceinline__ uint8_t lane_byte(const uint32_t (&e)[NG], int q, int
     return uint8_t(w >> (8 * L));
 }
 
-// The page and in-page offset of token t's slot; false for a slot that is
-// skipped (padding, outside the pool or the page table).
-__device__ __forceinline__ bool slot_of_token(const QuantizeParams& p, int64_t t, int64_t& page, int& off) {
-    const int64_t slot = p.slot_mapping[t];
+// The page and in-page offset of a slot; false for a slot that is skipped
+// (padding, outside the pool or the page table).
+__device__ __forceinline__ bool page_of_slot(const QuantizeParams& p, int64_t slot, int64_t& page, int& off) {
     if (slot < 0) return false;
     if (p.page_table != nullptr) {
         const int64_t per_seq = int64_t(p.max_pages_per_seq) * kPage;
@@ -270,20 +269,24 @@ __global__ void __launch_bounds__(256) quantize_kv_kernel(QuantizeParams p) {
     const int64_t t = int64_t(wi / unsigned(p.num_kv_heads)) * 16 + ((threadIdx.x & 63) >> 2);
     if (t >= p.num_tokens) return;   // whole quads leave together
 
-    // The rows are loaded together with the slot, before the slot is known
-    // to be valid: the row loads then overlap the slot and page-table
-    // lookups instead of waiting behind them (a padding token's row is read
-    // for nothing).
+    // K's row is loaded before the page of the slot is looked up, whether or not
+    // it is valid: the load overlaps the page-table lookup and its division
+    // instead of waiting behind them (a padding token's row is read for
+    // nothing).  V's follows the lookup: loads are waited for in their order, so
+    // that the page id would wait for V too, and K's encoding with it.
+    // bf16, K and V first / both after the lookup / this: 2309 tokens, 4 heads,
+    // paged 4.16 / 4.24 / 4.16 us; 16384 tokens, 8 heads 16.4 / 17.0 / 15.9; 65536
+    // tokens, 8 heads 69.0 / 67.9 / 66.2.
+    const int64_t slot = p.slot_mapping[t];
     const int64_t row = t * p.token_stride + int64_t(h) * D + 8 * L;
-    int64_t page;
-    int off;
-    const bool valid = slot_of_token(p, t, page, off);
     float xk[NG][8], xv[NG][8];
 #pragma unroll
-    for (int j = 0; j < NG; ++j) {
-        load_x8<DT>(p.k, row + 32 * j, xk[j]);
-        load_x8<DT>(p.v, row + 32 * j, xv[j]);
-    }
+    for (int j = 0; j < NG; ++j) load_x8<DT>(p.k, row + 32 * j, xk[j]);
+    int64_t page;
+    int off;
+    const bool valid = page_of_slot(p, slot, page, off);
+#pragma unroll
+    for (int j = 0; j < NG; ++j) load_x8<DT>(p.v, row + 32 * j, xv[j]);
     if (!valid) return;
 
     uint32_t wk[NG], wv[NG], bk[NG], bv[NG];
@@ -330,10 +333,13 @@ __global__ void __launch_bounds__(256) quantize_kv_d256_kernel(QuantizeParams p)
         load_x8<DT>(base, row, *reinterpret_cast<float(*)[8]>(&r[0]));
         load_x8<DT>(base, row + 8, *reinterpret_cast<float(*)[8]>(&r[8]));
     };
+    // K's row before the lookup, V's after it, as in quantize_kv_kernel (4096
+    // tokens of 8 heads 11.6 us, 12.9 with both before, 11.9 with both after)
+    const int64_t slot = p.slot_mapping[t];
+    load(p.k, x);
     int64_t page;
     int off;
-    const bool valid = slot_of_token(p, t, page, off);
-    load(p.k, x);
+    const bool valid = page_of_slot(p, slot, page, off);
     load(p.v, xv);
     if (!valid) return;
     const int64_t ph = page * p.num_kv_heads + h;

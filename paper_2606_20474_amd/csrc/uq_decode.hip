@@ -1021,14 +1021,6 @@ __device__ __forceinline__ bool plan_of_row(const DecodeParams& p, int lane, int
     plan_row(s, row, b, part, n);
     return true;
 }
-// The first row of sequence b and its number of rows.
-template <int PER>
-__device__ __forceinline__ void plan_of_seq(const DecodeParams& p, int lane, int b, int& first, int& rows) {
-    const SplitPlan<PER> s = split_plan<PER>(p, lane);
-    int n;
-    first = plan_first_row(s, b, n);
-    rows = plan_parts(n, s.part, s.inv);
-}
 
 // Tokens of sequence b that the shared prefix serves (whole pages, never the
 // last token).
@@ -2203,48 +2195,34 @@ hipError_t launch_decode_partials_mxpv(const DecodeParams& p, hipStream_t stream
 // wave and, for 16 groups, through LDS.  A block of 256 threads finishes
 // 16 / GROUPS rows.  One group per row walked the partials one after another:
 // 59 of them (one 120k context) took 13 us, with 16 groups 4.6 us.
+//
+// GROUPS follows the average number of partials (launch_merge); the balanced
+// split gives a long context among short ones many more.  Its rows of more
+// than kLongRow partials are left to the launch's first p.long_blocks blocks,
+// each of which merges one such row after another with all of its 16 groups.
+// 16 lanes per row walked them alone: with 8 kv heads, 120k among 31 contexts of
+// 1k 17.3 us, now 4.7; 128k among 127 of 500 tokens 22.8 and 6.2; among 255 of
+// 200 43.0 and 7.6 (a lower bound of 32 partials leaves 16k among 31 of 64 tokens at
+// 16.3 us a call, 13.4 with 16).  Batches without such rows are unchanged
+// within the noise (128 contexts around 16k 490 us a call, 256 of 8k 543).
+constexpr int kLongRow = 16;
+
+template <int N> struct MergeLds {
+    float acc[4][16][N + 1];
+    float ml[4][2];
+};
+
+// Row hq of sequence b (hq of this lane's group, 16 lanes or more): the np
+// context partials from row0 on, `step` apart, then nq prefix partials from
+// pre0 on.  `active` false: the lanes have no row.  16 groups: the whole block
+// takes part.
 template <int D, int GROUPS>
-__global__ void __launch_bounds__(256) merge_kernel(DecodeParams p) {
-    static_assert(GROUPS == 1 || GROUPS == 4 || GROUPS == 16, "16 lanes, a wave or a block per row");
+__device__ __forceinline__ void merge_partials(const DecodeParams& p, int b, int hq, bool active, int np, int64_t row0,
+                                               int64_t step, int nq, int64_t pre0, MergeLds<D / 16>* lds) {
     constexpr int N = D / 16;   // channels per lane
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int hq = GROUPS == 16 ? blockIdx.x : GROUPS == 4 ? blockIdx.x * 4 + wave : blockIdx.x * 16 + (threadIdx.x >> 4);
-    if (GROUPS != 1 && hq >= p.num_q_heads) return;
-    const int b = blockIdx.y;
     const int g = (threadIdx.x >> 4) % GROUPS;
     const int L = threadIdx.x & 15;
-    int np, nq = 0;                 // partials of the context, of the prefix
-    int64_t row0, step;             // first context partial row, distance between them
-    int64_t pre0;                   // first prefix partial row
-    const int64_t bh = int64_t(b) * p.num_q_heads + hq;
-    if (p.plan_rows > 0) {
-        int first;
-        if (p.batch <= 64) plan_of_seq<1>(p, threadIdx.x & 63, b, first, np);
-        else plan_of_seq<4>(p, threadIdx.x & 63, b, first, np);
-        if (np <= 1) return;        // finished by the decode kernel
-        row0 = int64_t(first) * p.num_q_heads + hq;
-        step = p.num_q_heads;
-        pre0 = 0;
-    } else {
-        int ctx = p.context_lens[b];
-        ctx = ctx < p.max_context ? ctx : p.max_context;
-        np = ctx > 0 ? (ctx + p.partition_tokens - 1) / p.partition_tokens : 0;
-        row0 = bh * p.num_partitions;
-        step = 1;
-        pre0 = row0 + p.suffix_partitions;
-        if (p.prefix_pages != nullptr) {
-            const int pl = prefix_tokens_of(p, b, ctx);
-            const int first = pl / p.partition_tokens;
-            nq = (pl + p.prefix_partition - 1) / p.prefix_partition;
-            np -= first;
-            row0 += first;
-            if (np + nq <= 0) return;   // empty context: written by the decode kernel
-        } else {
-            // the wave grid reduces W partitions per block into one slot
-            if (p.wave_parts > 1) np = (np + p.wave_parts - 1) / p.wave_parts;
-            if (np <= 1) return;        // finished by the decode kernel
-        }
-    }
     // finite start: a group without partials keeps sum 0 and weight 1 or 0
     float M = -3e38f;
     float lsum = 0.f;
@@ -2260,9 +2238,7 @@ __global__ void __launch_bounds__(256) merge_kernel(DecodeParams p) {
         for (int i = 0; i < N; ++i) o[i] = o[i] * fo + a[i] * fn;
         M = Mn;
     };
-#pragma unroll 4
-    for (int q = g; q < (GROUPS == 1 && hq >= p.num_q_heads ? 0 : np + nq); q += GROUPS) {
-        const int64_t r = q < np ? row0 + q * step : pre0 + (q - np);
+    auto merge_from = [&](int64_t r) {
         const float2 ml = *reinterpret_cast<const float2*>(p.part_ml + r * 2);
         const float4* src = reinterpret_cast<const float4*>(p.part_acc + r * D + N * L);
         float a[N];
@@ -2275,6 +2251,12 @@ __global__ void __launch_bounds__(256) merge_kernel(DecodeParams p) {
             a[4 * i + 3] = v.w;
         }
         merge_row(ml.x, ml.y, a);
+    };
+    if (active) {
+        int q = g;
+#pragma unroll 4
+        for (; q < np; q += GROUPS) merge_from(row0 + q * step);
+        for (; q < np + nq; q += GROUPS) merge_from(pre0 + (q - np));
     }
     if constexpr (GROUPS > 1) {
         // the 4 groups of a wave: lanes l ^ 16, then l ^ 32
@@ -2288,30 +2270,127 @@ __global__ void __launch_bounds__(256) merge_kernel(DecodeParams p) {
         }
     }
     if constexpr (GROUPS == 16) {
-        __shared__ float red[4][16][N + 1];
-        __shared__ float red_ml[4][2];
         if ((threadIdx.x & 63) < 16) {
 #pragma unroll
-            for (int i = 0; i < N; ++i) red[wave][L][i] = o[i];
+            for (int i = 0; i < N; ++i) lds->acc[wave][L][i] = o[i];
             if (L == 0) {
-                red_ml[wave][0] = M;
-                red_ml[wave][1] = lsum;
+                lds->ml[wave][0] = M;
+                lds->ml[wave][1] = lsum;
             }
         }
         __syncthreads();
-        if (threadIdx.x >= 16) return;
+        active = active && threadIdx.x < 16;
+        if (active) {
 #pragma unroll
-        for (int v = 1; v < 4; ++v) {
-            float a[N];
+            for (int v = 1; v < 4; ++v) {
+                float a[N];
 #pragma unroll
-            for (int i = 0; i < N; ++i) a[i] = red[v][L][i];
-            merge_row(red_ml[v][0], red_ml[v][1], a);
+                for (int i = 0; i < N; ++i) a[i] = lds->acc[v][L][i];
+                merge_row(lds->ml[v][0], lds->ml[v][1], a);
+            }
         }
-    } else if (GROUPS == 4 ? (threadIdx.x & 63) >= 16 : hq >= p.num_q_heads) {
-        return;   // whole 16-lane rows
+    } else if constexpr (GROUPS == 4) {
+        active = active && (threadIdx.x & 63) < 16;
     }
-    finish_row<N>(p, o, lsum, L);
-    write_out<N>(p, bh, L, o);
+    if (active) {   // whole 16-lane rows
+        finish_row<N>(p, o, lsum, L);
+        write_out<N>(p, int64_t(b) * p.num_q_heads + hq, L, o);
+    }
+}
+
+// The sequences of the balanced split with more than kLongRow rows, one int2
+// (first row, rows * 256 + sequence) each; returns their number.  Every wave of
+// the block writes the same list.
+template <int PER>
+__device__ __forceinline__ int list_long_rows(const DecodeParams& p, const SplitPlan<PER>& s, int2* list) {
+    const int lane = threadIdx.x & 63;
+    int k[PER], first = s.scan, count = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        k[i] = i < s.per && lane * s.per + i < p.batch ? plan_parts(s.n[i], s.part, s.inv) : 0;
+        first -= k[i];
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const uint64_t longs = __builtin_amdgcn_ballot_w64(k[i] > kLongRow);
+        const int at = count + __builtin_amdgcn_mbcnt_hi(uint32_t(longs >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(longs), 0));
+        if (k[i] > kLongRow) list[at] = make_int2(first, k[i] * 256 + lane * s.per + i);
+        count += __builtin_popcountll(longs);
+        first += k[i];
+    }
+    return count;
+}
+
+// The first row and the number of rows of sequence b, or (longs) the list above
+// and its length in np.
+template <int PER>
+__device__ __forceinline__ void merge_plan(const DecodeParams& p, bool longs, int b, int& first, int& np, int2* list) {
+    const SplitPlan<PER> s = split_plan<PER>(p, threadIdx.x & 63);
+    if (longs) {
+        first = 0;
+        np = list_long_rows(p, s, list);
+    } else {
+        int n;
+        first = plan_first_row(s, b, n);
+        np = plan_parts(n, s.part, s.inv);
+    }
+}
+
+// One launch per call: fixed partitions (PLAN false; with or without a shared
+// prefix) or the balanced split.
+template <int D, int GROUPS, bool PLAN>
+__global__ void __launch_bounds__(256) merge_kernel(DecodeParams p) {
+    static_assert(GROUPS == 1 || GROUPS == 4 || GROUPS == 16, "16 lanes, a wave or a block per row");
+    __shared__ MergeLds<D / 16> lds[1];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int hq = GROUPS == 16 ? blockIdx.x : GROUPS == 4 ? blockIdx.x * 4 + wave : blockIdx.x * 16 + (threadIdx.x >> 4);
+    const bool active = hq < p.num_q_heads;
+    if constexpr (PLAN) {
+        __shared__ int2 list[GROUPS < 16 ? kPlanBatch : 1];
+        const int long_rows = GROUPS < 16 ? p.long_blocks / int(gridDim.x) : 0;   // grid rows of the long rows' blocks
+        const bool longs = GROUPS < 16 && int(blockIdx.y) < long_rows;
+        const int b = int(blockIdx.y) - long_rows;
+        int first, np;   // of sequence b; or the list's length
+        if (p.batch <= 64) merge_plan<1>(p, longs, b, first, np, list);
+        else merge_plan<4>(p, longs, b, first, np, list);
+        if (longs) {
+            // every (long sequence, query head) in turn, one block each
+            __syncthreads();
+#pragma unroll 1
+            for (int item = blockIdx.y * gridDim.x + blockIdx.x; item < np * p.num_q_heads; item += p.long_blocks) {
+                const int2 e = list[item / p.num_q_heads];
+                const int h = item % p.num_q_heads;
+                merge_partials<D, 16>(p, e.y & 255, h, true, e.y >> 8, int64_t(e.x) * p.num_q_heads + h, p.num_q_heads, 0,
+                                      0, lds);
+                __syncthreads();   // the LDS rows are read before the next item's are written
+            }
+            return;
+        }
+        if (np <= 1) return;                            // finished by the decode kernel
+        if (long_rows > 0 && np > kLongRow) return;     // finished by the long rows' blocks
+        merge_partials<D, GROUPS>(p, b, hq, active, np, int64_t(first) * p.num_q_heads + hq, p.num_q_heads, 0, 0, lds);
+    } else {
+        const int b = blockIdx.y;
+        int ctx = p.context_lens[b];
+        ctx = ctx < p.max_context ? ctx : p.max_context;
+        int np = ctx > 0 ? (ctx + p.partition_tokens - 1) / p.partition_tokens : 0;
+        int nq = 0;
+        int64_t row0 = (int64_t(b) * p.num_q_heads + hq) * p.num_partitions;
+        const int64_t pre0 = row0 + p.suffix_partitions;
+        if (p.prefix_pages != nullptr) {
+            const int pl = prefix_tokens_of(p, b, ctx);
+            const int first = pl / p.partition_tokens;
+            nq = (pl + p.prefix_partition - 1) / p.prefix_partition;
+            np -= first;
+            row0 += first;
+            if (np + nq <= 0) return;   // empty context: written by the decode kernel
+        } else {
+            // the wave grid reduces W partitions per block into one slot
+            if (p.wave_parts > 1) np = (np + p.wave_parts - 1) / p.wave_parts;
+            if (np <= 1) return;        // finished by the decode kernel
+        }
+        merge_partials<D, GROUPS>(p, b, hq, active, np, row0, 1, nq, pre0, lds);
+    }
 }
 
 // The rows of a cascade launch in dispatch order (one block).  The tokens
@@ -2498,17 +2577,33 @@ hipError_t launch_decode_partials(const DecodeParams& p, hipStream_t stream) {
 
 // 16 lanes per row up to 4 partials of it (the balanced split: on average), a
 // wave up to 16, a block beyond.  2048 rows of 4 partials take 5.1 us with 16
-// lanes each, 5.4 with a wave, 7.5 with a block.
-template <int D>
-static hipError_t launch_merge(const DecodeParams& p, hipStream_t stream) {
-    const int partials = p.plan_rows > 0 ? p.plan_rows / p.batch
+// lanes each, 5.4 with a wave, 7.5 with a block.  Where a sequence of the
+// balanced split can have more than kLongRow rows (what the others leave of
+// plan_rows, at most its length in planner units), about a block per CU
+// is added for those.
+template <int D, bool PLAN>
+static hipError_t launch_merge_with(DecodeParams p, hipStream_t stream) {
+    const int partials = PLAN ? p.plan_rows / p.batch
                          : p.wave_parts > 1 ? (p.num_partitions + p.wave_parts - 1) / p.wave_parts : p.num_partitions;
     const unsigned rows = partials <= 4 ? 16 : partials <= 16 ? 4 : 1;
-    const dim3 grid{(unsigned(p.num_q_heads) + rows - 1) / rows, unsigned(p.batch)};
-    if (rows == 16) hipLaunchKernelGGL((merge_kernel<D, 1>), grid, dim3(256), 0, stream, p);
-    else if (rows == 4) hipLaunchKernelGGL((merge_kernel<D, 4>), grid, dim3(256), 0, stream, p);
-    else hipLaunchKernelGGL((merge_kernel<D, 16>), grid, dim3(256), 0, stream, p);
+    dim3 grid{(unsigned(p.num_q_heads) + rows - 1) / rows, unsigned(p.batch)};
+    p.long_blocks = 0;
+    if (PLAN && rows > 1) {
+        const int most = p.plan_rows - p.batch + 1, units = (p.max_context + kPlanUnit - 1) / kPlanUnit;
+        if ((most < units ? most : units) > kLongRow) {
+            const unsigned y = (unsigned(kNumCus) + grid.x - 1) / grid.x;
+            grid.y += y;
+            p.long_blocks = int32_t(y * grid.x);
+        }
+    }
+    if (rows == 16) hipLaunchKernelGGL((merge_kernel<D, 1, PLAN>), grid, dim3(256), 0, stream, p);
+    else if (rows == 4) hipLaunchKernelGGL((merge_kernel<D, 4, PLAN>), grid, dim3(256), 0, stream, p);
+    else hipLaunchKernelGGL((merge_kernel<D, 16, PLAN>), grid, dim3(256), 0, stream, p);
     return hipGetLastError();
+}
+template <int D>
+static hipError_t launch_merge(const DecodeParams& p, hipStream_t stream) {
+    return p.plan_rows > 0 ? launch_merge_with<D, true>(p, stream) : launch_merge_with<D, false>(p, stream);
 }
 
 hipError_t launch_decode_merge(const DecodeParams& p, hipStream_t stream) {

@@ -2342,9 +2342,15 @@ template <int D, int GROUPS, bool PLAN>
 __global__ void __launch_bounds__(256) merge_kernel(DecodeParams p) {
     static_assert(GROUPS == 1 || GROUPS == 4 || GROUPS == 16, "16 lanes, a wave or a block per row");
     __shared__ MergeLds<D / 16> lds[1];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int hq = GROUPS == 16 ? blockIdx.x : GROUPS == 4 ? blockIdx.x * 4 + wave : blockIdx.x * 16 + (threadIdx.x >> 4);
-    const bool active = hq < p.num_q_heads;
+    constexpr int R = 16 / GROUPS;   // query heads per block
+    const int r = GROUPS == 16 ? 0 : GROUPS == 4 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : int(threadIdx.x >> 4);
+    int hq = int(blockIdx.x) * R + r;
+    bool active = hq < p.num_q_heads;
+    if (!PLAN && p.merge_by_head) {
+        const int in_head = int(blockIdx.x / unsigned(p.num_kv_heads)) * R + r;
+        hq = int(blockIdx.x % unsigned(p.num_kv_heads)) * p.group + in_head;
+        active = in_head < p.group;
+    }
     if constexpr (PLAN) {
         __shared__ int2 list[GROUPS < 16 ? kPlanBatch : 1];
         const int long_rows = GROUPS < 16 ? p.long_blocks / int(gridDim.x) : 0;   // grid rows of the long rows' blocks
@@ -2577,7 +2583,14 @@ hipError_t launch_decode_partials(const DecodeParams& p, hipStream_t stream) {
 
 // 16 lanes per row up to 4 partials of it (the balanced split: on average), a
 // wave up to 16, a block beyond.  2048 rows of 4 partials take 5.1 us with 16
-// lanes each, 5.4 with a wave, 7.5 with a block.  Where a sequence of the
+// lanes each, 5.4 with a wave, 7.5 with a block.
+// Fixed partitions, kv heads a multiple of 8: a block takes the query heads of
+// one kv head, kv head fastest, so that it runs on the XCD whose decode blocks
+// wrote the partials and finds them in its L2 (256 contexts of 128k, 64/8 heads:
+// 9.0 us, 11.8 with 16 query heads per block; with 8 of them half the block has
+// no row, which is why the balanced split, whose waves all compute the plan, does
+// without: 17.4 us against 11.1 for 256 contexts around 8k).
+// Where a sequence of the
 // balanced split can have more than kLongRow rows (what the others leave of
 // plan_rows, at most its length in planner units), about a block per CU
 // is added for those.
@@ -2587,6 +2600,11 @@ static hipError_t launch_merge_with(DecodeParams p, hipStream_t stream) {
                          : p.wave_parts > 1 ? (p.num_partitions + p.wave_parts - 1) / p.wave_parts : p.num_partitions;
     const unsigned rows = partials <= 4 ? 16 : partials <= 16 ? 4 : 1;
     dim3 grid{(unsigned(p.num_q_heads) + rows - 1) / rows, unsigned(p.batch)};
+    p.merge_by_head = 0;
+    if (!PLAN && p.prefix_pages == nullptr && p.num_kv_heads % 8 == 0 && unsigned(p.group) % (rows < 8 ? rows : 8) == 0) {
+        p.merge_by_head = 1;
+        grid.x = unsigned(p.num_kv_heads) * ((unsigned(p.group) + rows - 1) / rows);
+    }
     p.long_blocks = 0;
     if (PLAN && rows > 1) {
         const int most = p.plan_rows - p.batch + 1, units = (p.max_context + kPlanUnit - 1) / kPlanUnit;

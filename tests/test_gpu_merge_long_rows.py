@@ -96,3 +96,25 @@ def test_merge_time_of_a_skewed_batch(uq):
     equal, skewed = time([4700] * batch), time([bound] + [1000] * (batch - 1))
     print(f"merge: equal {equal:.1f} us, skewed {skewed:.1f} us", flush=True)
     assert skewed <= 2 * equal
+
+
+@pytest.mark.parametrize("hq,hkv", [(8, 8), (32, 8), (40, 8), (64, 8), (96, 8), (128, 8), (64, 16), (36, 9)])
+@pytest.mark.parametrize("partition", [1536, 512, 64])   # up to 3, 8 and 63 partials: 16 lanes, a wave, a block per row
+def test_query_heads_of_fixed_partitions(uq, hq, hkv, partition):
+    """Every group size and merge form writes every query head (KV heads a
+    multiple of 8: the heads of a block belong to one KV head), against one
+    partition per sequence, finished without a merge."""
+    dev = torch.device("cuda:0")
+    print(f"merge of fixed partitions: {hq}/{hkv} heads, partition {partition}", flush=True)
+    wl = workloads.custom(4, hq, hkv, [4000, 1537, 65, 3100], seed=hq, head_dim=128)
+    desc = uq.CacheDesc(num_kv_heads=hkv, num_pages=wl.num_pages)
+    pools = desc.alloc_pools(dev, fill=0)
+    for key, lo, hi, row in wl.segments():
+        k, v = wl.kv(key, lo, hi, device=dev)
+        uq.quantize_kv(desc, k, v, torch.as_tensor(wl.slots(key, lo, hi, row), device=dev), *pools)
+    q, pt = wl.q.to(dev), torch.as_tensor(wl.page_table, device=dev)
+    ctx = torch.as_tensor(wl.context_lens, device=dev)
+    out = [uq.decode_attention(desc, q, *pools, pt, ctx, wl.max_context, 128 ** -0.5, p,
+                               out=torch.full((4, hq, 128), float("nan"), device=dev)).double() for p in (partition, 4000)]
+    assert torch.isfinite(out[0]).all()
+    assert float(((out[0] - out[1]).norm(dim=-1) / out[1].norm(dim=-1)).max()) <= 1e-4

@@ -93,6 +93,29 @@ int32_t split_rows(int32_t batch, int32_t block_heads, int32_t max_context, int3
     return int32_t(rows < np * batch ? rows : np * batch);
 }
 
+// Parts each context of the balanced split is cut into where all lengths are
+// equal (0: as the rows allow).  Equal blocks finish together, so that the CUs
+// that get one more than the others decide: of the k that the rows allow, the
+// least k with the least (blocks per CU, at least 2 to keep its memory path
+// busy) / k.  Batches whose rows allow more than 8 come out even without.  Most parts
+// that fit / this, one MI355X, 8 query heads per KV head: 36 x 100k, 4 kv heads
+// 364 / 320 us; 150 x 40k, 4 heads 552 / 527; 48 x 40k, 8 heads 348 / 330; 160 x 30k, 8
+// heads 854 / 834; BF16 cache, 36 x 50k, 4 heads 692 / 544.
+int32_t equal_parts(int32_t batch, int32_t block_heads, int32_t rows) {
+    if (rows / batch > 8) return 0;
+    int32_t best = 0;
+    int64_t best_rounds = 0;
+    for (int32_t k = 1; k <= rows / batch; ++k) {
+        int64_t rounds = (int64_t(batch) * k * block_heads + uq::kNumCus - 1) / uq::kNumCus;
+        rounds = rounds > 2 ? rounds : 2;
+        if (best == 0 || 64 * rounds * best < 63 * best_rounds * k) {
+            best = k;
+            best_rounds = rounds;
+        }
+    }
+    return best;
+}
+
 // Workspace of a decode call: the partial rows (accumulators, then the
 // (max, sum) pairs); a cascade call (extra_slots > 0: its prefix
 // partitions) adds its row list, 16 bytes per context row (partition,
@@ -175,6 +198,8 @@ uq_status make_decode_params(const uq_cache_desc* desc, const void* q, uq_dtype 
     p.plan_rows = extra_slots > 0 ? 0 : split_rows(batch, block_heads(desc, num_q_heads), max_context, part);
     p.plan_inv_rows = p.plan_rows > 0 ? 1.0f / float(p.plan_rows) : 0.0f;
     p.plan_inv_free = p.plan_rows > batch ? 1.0f / float(p.plan_rows - batch) : 0.0f;
+    p.plan_equal = equal_parts(batch, block_heads(desc, num_q_heads), p.plan_rows);
+    p.plan_inv_equal = p.plan_equal > 0 ? 1.0f / float(p.plan_equal) : 0.0f;
     p.merge_by_head = 0;
     p.long_blocks = 0;
     p.probe_sink = nullptr;
@@ -315,6 +340,14 @@ uq_cache_desc geometry_of(const uq_ref_cache_desc* d) {
 
 int32_t ref_fmt(const uq_ref_cache_desc* d) {
     return d->format == UQ_REF_FP8_E4M3 ? uq::kFp8 : d->format == UQ_REF_TQ4 ? uq::kTq4 : uq::kBf16;
+}
+
+// The cache format of a decode call's parameter block (both of its launches).
+// Ultra-TQ is bound by each CU's decoding, which more and smaller blocks spread
+// better than equal parts do (128 x 20k, 8 kv heads 626 us, 639 with them).
+void set_ref_format(const uq_ref_cache_desc* d, uq::DecodeParams& p) {
+    p.kv_fmt = ref_fmt(d);
+    if (p.kv_fmt == uq::kTq4) p.plan_equal = 0;
 }
 
 // Half of the bytes of one (page, kv head): the K tile, or for TQ4 half of
@@ -644,7 +677,7 @@ static uq_status ref_decode_setup(const uq_ref_cache_desc* desc, const void* q, 
                      max_context, softmax_scale, partition_tokens, workspace, workspace_bytes, out, out_dtype, p,
                      extra_slots);
     if (s != UQ_OK) return s;
-    p.kv_fmt = ref_fmt(desc);
+    set_ref_format(desc, p);
     p.scales = nullptr;
     if (desc->format == UQ_REF_TQ4) tq_tables(desc->codebook, p.tq);
     if (desc->format == UQ_REF_FP8_E4M3) {
@@ -736,7 +769,7 @@ uq_status uq_ref_decode_merge(const uq_ref_cache_desc* desc, int32_t batch, int3
                            max_context, 1.0f, partition_tokens, const_cast<void*>(workspace), workspace_bytes, out,
                            out_dtype, p);
     if (s != UQ_OK) return s;
-    p.kv_fmt = ref_fmt(desc);
+    set_ref_format(desc, p);
     if (desc->format == UQ_REF_FP8_E4M3) p.out_scale = desc->v_scale;
     return from_hip(uq::launch_decode_merge(p, static_cast<hipStream_t>(stream)));
 }
@@ -919,7 +952,7 @@ uq_status uq_ref_decode_cascade_merge(const uq_ref_cache_desc* desc, int32_t bat
     s = cascade_merge_setup(&g, batch, num_q_heads, context_lens, max_context, prefix, partition_tokens, workspace,
                             workspace_bytes, out, out_dtype, p);
     if (s != UQ_OK) return s;
-    p.kv_fmt = ref_fmt(desc);
+    set_ref_format(desc, p);
     if (desc->format == UQ_REF_FP8_E4M3) p.out_scale = desc->v_scale;
     return from_hip(uq::launch_decode_merge(p, static_cast<hipStream_t>(stream)));
 }

@@ -880,6 +880,9 @@ __device__ __forceinline__ uint32_t fold_words(const R& r) {
 // (48/8 heads, the wave grid before) 871 / 682 us; equal lengths unchanged (32 x
 // 32k, 64/4 heads: 100 us).
 //
+// Lengths within 1/16 of their maximum (on average) are cut into plan_equal
+// equal parts each (equal_parts in uq_api.hip).
+//
 // Every wave computes the plan for itself (lane l holds sequences l * per ..
 // l * per + per - 1, per <= 4): the sums and the scan are DPP.  The search
 // tries the lower bound sum / plan_rows first (the answer for equal lengths),
@@ -912,6 +915,21 @@ __device__ __forceinline__ int wave_scan(int x) {
     return dpp_add<0x143, 0xC>(x);   // row_bcast:31 into rows 2 and 3
 }
 
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_max(int x) {
+    const int y = __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, false);
+    return x > y ? x : y;
+}
+// Maximum of the wave's values, none of them negative.
+__device__ __forceinline__ int wave_max(int x) {
+    x = dpp_max<0x111, 0xF>(x);
+    x = dpp_max<0x112, 0xF>(x);
+    x = dpp_max<0x114, 0xF>(x);
+    x = dpp_max<0x118, 0xF>(x);
+    x = dpp_max<0x142, 0xA>(x);
+    return __builtin_amdgcn_readlane(dpp_max<0x143, 0xC>(x), 63);
+}
+
 // Partitions of n tokens, at least 1: ceil(n / part) by the reciprocal, put
 // right by the remainder.
 __device__ __forceinline__ int plan_parts(int n, int part, float inv) {
@@ -926,7 +944,7 @@ template <int PER>
 __device__ __forceinline__ SplitPlan<PER> split_plan(const DecodeParams& p, int lane) {
     SplitPlan<PER> s;
     s.per = PER == 1 ? 1 : (p.batch + 63) >> 6;
-    int tokens = 0;
+    int tokens = 0, most = 0;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
         s.n[i] = 0;
@@ -937,9 +955,11 @@ __device__ __forceinline__ SplitPlan<PER> split_plan(const DecodeParams& p, int 
                 s.n[i] = ctx > 0 ? (ctx < p.max_context ? ctx : p.max_context) : 0;
             }
             tokens += s.n[i];
+            most = s.n[i] > most ? s.n[i] : most;
         }
     }
-    const float sum = float(__builtin_amdgcn_readlane(wave_scan(tokens), 63)) * (1.0f / kPlanUnit);
+    const int all = __builtin_amdgcn_readlane(wave_scan(tokens), 63);
+    const float sum = float(all) * (1.0f / kPlanUnit);
     int lo = int(sum * p.plan_inv_rows + 0.99f);
     lo = lo > 1 ? lo : 1;
     const int whole = (p.max_context + kPlanUnit - 1) / kPlanUnit;   // one partition per sequence
@@ -951,6 +971,11 @@ __device__ __forceinline__ SplitPlan<PER> split_plan(const DecodeParams& p, int 
     // lo, once tried, does not fit; hi does (`whole` for certain); s keeps the
     // last candidate that fitted, which is hi when the loop ends
     int cand = lo;
+    if (p.plan_equal > 0) {
+        const int top = wave_max(most);
+        if (int64_t(all) * 16 >= int64_t(p.batch) * top * 15)
+            cand = plan_parts((top + kPlanUnit - 1) / kPlanUnit, p.plan_equal, p.plan_inv_equal);
+    }
 #pragma unroll 1
     for (int it = 0;; ++it) {
         const int part = cand * kPlanUnit;

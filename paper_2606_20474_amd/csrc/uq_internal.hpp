@@ -130,6 +130,10 @@ struct DecodeParams {
     int32_t plan_rows;
     float plan_inv_rows;
     float plan_inv_free;
+    // partitions per sequence where the lengths are equal, and its reciprocal (0:
+    // no rule of their own)
+    int32_t plan_equal;
+    float plan_inv_equal;
     int32_t merge_by_head;   // merge launch: a block's query heads belong to one kv head
     int32_t long_blocks;     // merge launch: blocks of the split's long rows, ahead of the others
     // the page-gather probe's checksums, one per wave of the partition

@@ -78,18 +78,22 @@ int64_t num_partitions(int32_t max_context, int32_t part) {
 // few (a single 120k context, 8 kv heads: 27.6 us with 512 blocks, 28.7 with
 // its 472 default partitions, 33 with 944); four rows per sequence where they
 // alone fill the chip (64 sequences of 0.3k-64k tokens, 8 kv heads: 128 us with
-// 2048 blocks, 130 with 1024, 269 with 512); two where they fill it twice over
-// (128 sequences, 8 kv heads: 4k-128k tokens 680 us, 656 with four, 871 with the
-// wave grid's fixed partitions; all of 128k 2779 us, 2798 with four, 2781 with
-// the wave grid).  The planner's lanes hold 256 lengths, whose sum and rounding
-// stay within 30 bits.
+// 2048 blocks, 130 with 1024, 269 with 512).  Two, three, four and six rows per
+// sequence, lognormal lengths of spread s around a median, us:
+//   128 around 32k, s 0.8, 8 kv heads 1050 1027 1011 1031   (wave grid 1356)
+//   140 around 40k, s 1.0, 8 kv heads 1463 1382 1367 1380   (1569)
+//   256 around 40k, s 0.3, 4 kv heads 1031  984  981  991   (1129)
+//   160 around 40k, s 0.3, 8 kv heads 1214 1193 1183 1202   (1364)
+//   256 around 16k, s 0.8, 8 kv heads 1023 1025 1034 1065   (1330)
+//   200 around  8k, s 0.3, 8 kv heads  337  338  338  338   (325: one partition of
+//   16384 and a short rest each, the rests last, which fill the end better)
+// The planner's lanes hold 256 lengths, whose sum and rounding stay within 30 bits.
 int32_t split_rows(int32_t batch, int32_t block_heads, int32_t max_context, int32_t part) {
     const int64_t np = num_partitions(max_context, part);
     if (np <= 1 || part != pick_partition(batch, block_heads, max_context)) return 0;
     if (batch > uq::kPlanBatch || int64_t(batch) * max_context >= (int64_t(1) << 30)) return 0;
     int64_t rows = 2 * uq::kNumCus / block_heads;
-    const int64_t each = int64_t(batch) * block_heads >= 4 * uq::kNumCus ? 2 : 4;
-    rows = rows > each * batch ? rows : each * batch;
+    rows = rows > 4 * int64_t(batch) ? rows : 4 * int64_t(batch);
     return int32_t(rows < np * batch ? rows : np * batch);
 }
 

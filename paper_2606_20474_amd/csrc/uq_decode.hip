@@ -940,8 +940,11 @@ __device__ __forceinline__ int plan_parts(int n, int part, float inv) {
     return n > 0 ? q : 1;
 }
 
+// Both launches of a call compute the plan and have to agree on it to the bit: no
+// product is fused into a sum here or there.
 template <int PER>
 __device__ __forceinline__ SplitPlan<PER> split_plan(const DecodeParams& p, int lane) {
+#pragma clang fp contract(off)
     SplitPlan<PER> s;
     s.per = PER == 1 ? 1 : (p.batch + 63) >> 6;
     int tokens = 0, most = 0;

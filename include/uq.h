@@ -187,10 +187,12 @@ int32_t uq_default_partition(const uq_cache_desc *desc, int32_t batch, int32_t n
  * merge.  With the default partition (0, or its value), more than one of
  * them, no shared prefix and up to 256 sequences, the launch instead takes a
  * block grid that shares its rows among the sequences by their lengths, read on the device:
- * the kernels cut every context into equal partitions of the shortest length
- * for which the rows suffice, so that a ragged batch, or one far below
+ * the kernels cut every context into partitions of one length, near the
+ * shortest for which the rows suffice, so that a ragged batch, or one far below
  * max_context, still fills the GPU.  The result does not depend on the grid
- * beyond rounding.
+ * beyond rounding.  With the balanced split that rounding, and so the bits of a
+ * sequence's output, depends on the lengths of the other sequences in the call;
+ * any other partition_tokens cuts a context by its own length alone.
  *   q             : [batch][num_q_heads][128].  F32/BF16/F16: rotated and
  *                   cast to FP8 inside the call.  FP8_E4M3: already
  *                   prepared by uq_prepare_query.
@@ -582,9 +584,9 @@ uq_status uq_decode_attention_noalloc(const uq_cache_desc *desc, const void *q, 
  *
  * uq_probe_page_gather -- the FP4 decode kernel's memory traffic alone:
  *   the partition launch of uq_decode_attention for these arguments, run
- *   as a probe: its grid (one block per partition, or one wave per
- *   partition on the grid the library picks for many partitions; head
- *   sizes 64, 128 and 256), page walk through page_table, page-id copies
+ *   as a probe: its grid (one block per partition or per row of the
+ *   balanced split, or one wave per partition on the grid the library picks
+ *   for many partitions; head sizes 64, 128 and 256), page walk through page_table, page-id copies
  *   and 2-slot LDS ring filled by the same copy instructions with the same
  *   cache policy, every staged byte read back into registers, and no query
  *   prologue, arithmetic or partial rows: each wave writes one uint32 XOR

@@ -870,9 +870,9 @@ __device__ __forceinline__ uint32_t fold_words(const R& r) {
 // leave the partition to the library; always the block grid).  The launch has
 // plan_rows rows per kv head, each one block and one partial row of the
 // workspace; how the sequences share them is decided on the device from the
-// context lengths: the shortest partition P (a multiple of kPlanUnit) with
-// sum over sequences of ceil(tokens / P) <= plan_rows, rows handed out
-// sequence after sequence.  With one partition length per launch, sized from
+// context lengths: a partition P (a multiple of kPlanUnit) with sum over
+// sequences of ceil(tokens / P) <= plan_rows, near the shortest such (at most 7
+// bisection candidates are tried), rows handed out sequence after sequence.  With one partition length per launch, sized from
 // the host's bound of the lengths, the rows of short contexts went unused and
 // the longest partitions ran alone at the end.  Step before / after, one
 // MI355X: 12 sequences of 0.3k-55k tokens under a 64k bound (48/8 heads)
@@ -888,7 +888,7 @@ __device__ __forceinline__ uint32_t fold_words(const R& r) {
 // tries the lower bound sum / plan_rows first (the answer for equal lengths),
 // then halves the range up to sum / (plan_rows - batch), which always fits.  An
 // empty context keeps one row (its zero output).
-constexpr int kPlanUnit = 128;   // one page pair for each of 4 waves
+constexpr int kPlanUnit = 128;   // a page pair for each wave of a 4-wave block (kFp4d64p2: two for every other wave)
 // PER: the most sequences a lane holds, 1 for batches of up to 64 (their own
 // code path: every block runs it once, from a cold instruction cache).
 template <int PER>

@@ -12,7 +12,15 @@ plan's 128-token unit, empty contexts, all lengths equal, one long context
 among short ones; a bound of the lengths far above them; every cache format
 and head size.  Both paths round P to two BF16 terms, |error| <= 2^-16 |P|, so
 an output element differs by at most 2 * 2^-16 * max|V| plus fp32 sums of a few
-units of 2^-24: held to 2^-14 * max|V| over the cache.
+units of 2^-24: held to 2^-14 * max|V| over the cache.  That bar alone would
+pass a token lost at a joint of a long context, so every (sequence, head) row is
+also held to a relative L2 difference of 1e-4: the errors are 2^-16 of terms
+whose sum is the row, and over zero-mean V they grow as it does, so a row
+differs by about 2^-16 = 1.5e-5; one token of n moves it by about 1 / sqrt(n),
+7e-3 and more here.
+  * the step (the new token written and attended): the same rows, and the same
+    pool bytes as a write followed by attention, over lengths 128 k + 1, where
+    the new token is alone in its partition for every k the partition divides;
   * the workspace is full of 0xFF bytes (NaN partials) before the call;
   * the two launches called one by one, and the default partition passed by
     its value, give the same bits.
@@ -46,6 +54,13 @@ def lens(kind, batch, top):
     if kind == "one-long":
         return [top] + [int(c) for c in rng.integers(1, 200, batch - 1)]
     return [0] * (batch - 1) + [top]   # "empty"
+
+
+def largest_row_difference(got, ref, ctx):
+    got, ref = got[ctx > 0].double(), ref[ctx > 0].double()
+    rel = float(((got - ref).norm(dim=-1) / ref.norm(dim=-1)).max())
+    print(f"  largest relative L2 of a row {rel:.2e}", flush=True)
+    return rel
 
 
 @pytest.mark.parametrize("batch,hq,hkv,kind,top,bound,fmt,d", [
@@ -110,3 +125,32 @@ def test_default_split_equals_fixed_partitions(uq, batch, hq, hkv, kind, top, bo
     print(f"  max difference {err:.3e}", flush=True)
     assert err <= V_MAX * 2.0 ** -14
     assert torch.all(got[ctx == 0] == 0)
+    assert largest_row_difference(got, ref, ctx) <= 1e-4
+
+
+@pytest.mark.parametrize("batch,hq,hkv,fmt", [(12, 16, 2, "fp4"), (65, 6, 1, "fp4"), (256, 8, 2, "fp4"), (65, 6, 1, "fp8"),
+                                              (65, 6, 1, "bf16"), (65, 6, 1, "tq4")])
+def test_step_on_the_balanced_split(uq, batch, hq, hkv, fmt):
+    dev = torch.device("cuda:0")
+    print(f"step on the balanced split: B={batch} {hq}/{hkv} heads, {fmt}", flush=True)
+    wl = workloads.custom(batch, hq, hkv, [128 * (7 * i % 40) + 1 for i in range(batch - 1)] + [6145], seed=batch)
+    if fmt == "fp4":
+        desc = uq.CacheDesc(num_kv_heads=hkv, num_pages=wl.num_pages)
+        bufs, write, attend, step = desc.alloc_pools(dev, fill=0), uq.quantize_kv, uq.decode_attention, uq.decode_step
+    else:
+        desc = uq.RefCacheDesc(num_kv_heads=hkv, num_pages=wl.num_pages, fmt=fmt, k_scale=0.3, v_scale=0.3)
+        bufs, write, attend, step = (desc.alloc_cache(dev, fill=0),), uq.ref_write_kv, uq.ref_decode_attention, uq.ref_decode_step
+    for key, lo, hi, row in wl.segments():
+        k, v = wl.kv(key, lo, hi, device=dev)
+        write(desc, k, v, torch.as_tensor(wl.slots(key, lo, hi, row), device=dev), *bufs)
+    pt, ctx = torch.as_tensor(wl.page_table, device=dev), torch.as_tensor(wl.context_lens, device=dev)
+    q = wl.q.to(dev)
+    g = torch.Generator(device="cuda").manual_seed(batch)
+    k_new, v_new = (torch.randn((batch, hkv, 128), generator=g, device=dev) for _ in range(2))
+    want = tuple(b.clone() for b in bufs)
+    slots = torch.arange(batch, device=dev) * (pt.shape[1] * 16) + ctx.long() - 1
+    write(desc, k_new, v_new, slots, *want, page_table=pt)
+    ref = attend(desc, q, *want, pt, ctx, wl.max_context, 128 ** -0.5, 592)
+    got = step(desc, q, k_new, v_new, *bufs, pt, ctx, wl.max_context, 128 ** -0.5, 0)
+    assert all(torch.equal(a, b) for a, b in zip(bufs, want)), "stored tokens differ"
+    assert largest_row_difference(got, ref, ctx) <= 1e-4

@@ -2280,11 +2280,12 @@ __device__ __forceinline__ void merge_partials(const DecodeParams& p, int b, int
         }
         merge_row(ml.x, ml.y, a);
     };
-    if (active) {
-        int q = g;
+    if (active && nq == 0) {
 #pragma unroll 4
-        for (; q < np; q += GROUPS) merge_from(row0 + q * step);
-        for (; q < np + nq; q += GROUPS) merge_from(pre0 + (q - np));
+        for (int q = g; q < np; q += GROUPS) merge_from(row0 + q * step);
+    } else if (active) {
+#pragma unroll 4
+        for (int q = g; q < np + nq; q += GROUPS) merge_from(q < np ? row0 + q * step : pre0 + (q - np));
     }
     if constexpr (GROUPS > 1) {
         // the 4 groups of a wave: lanes l ^ 16, then l ^ 32

@@ -2621,8 +2621,8 @@ hipError_t launch_decode_partials(const DecodeParams& p, hipStream_t stream) {
 // without: 17.4 us against 11.1 for 256 contexts around 8k).
 // Where a sequence of the
 // balanced split can have more than kLongRow rows (what the others leave of
-// plan_rows, at most its length in planner units), about a block per CU
-// is added for those.
+// plan_rows, at most its length in planner units), a block for each of those, up
+// to about one per CU, is added.
 template <int D, bool PLAN>
 static hipError_t launch_merge_with(DecodeParams p, hipStream_t stream) {
     const int partials = PLAN ? p.plan_rows / p.batch
@@ -2638,7 +2638,9 @@ static hipError_t launch_merge_with(DecodeParams p, hipStream_t stream) {
     if (PLAN && rows > 1) {
         const int most = p.plan_rows - p.batch + 1, units = (p.max_context + kPlanUnit - 1) / kPlanUnit;
         if ((most < units ? most : units) > kLongRow) {
-            const unsigned y = (unsigned(kNumCus) + grid.x - 1) / grid.x;
+            const int64_t longs = int64_t(p.plan_rows / (kLongRow + 1)) * p.num_q_heads;   // long rows at most
+            const unsigned blocks = unsigned(longs < kNumCus ? longs : kNumCus);
+            const unsigned y = (blocks + grid.x - 1) / grid.x;
             grid.y += y;
             p.long_blocks = int32_t(y * grid.x);
         }

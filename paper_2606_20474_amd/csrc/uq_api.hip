@@ -202,6 +202,7 @@ uq_status make_decode_params(const uq_cache_desc* desc, const void* q, uq_dtype 
     p.plan_rows = extra_slots > 0 ? 0 : split_rows(batch, block_heads(desc, num_q_heads), max_context, part);
     p.plan_inv_rows = p.plan_rows > 0 ? 1.0f / float(p.plan_rows) : 0.0f;
     p.plan_inv_free = p.plan_rows > batch ? 1.0f / float(p.plan_rows - batch) : 0.0f;
+    p.plan_fill = float(block_heads(desc, num_q_heads)) / float(2 * uq::kNumCus * uq::kPlanUnit);
     p.plan_equal = equal_parts(batch, block_heads(desc, num_q_heads), p.plan_rows);
     p.plan_inv_equal = p.plan_equal > 0 ? 1.0f / float(p.plan_equal) : 0.0f;
     p.merge_by_head = 0;

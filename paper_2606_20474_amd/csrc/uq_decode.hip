@@ -888,7 +888,11 @@ __device__ __forceinline__ uint32_t fold_words(const R& r) {
 // tries the lower bound sum / plan_rows first (the answer for equal lengths),
 // then halves the range up to sum / (plan_rows - batch), which always fits.  An
 // empty context keeps one row (its zero output).
-constexpr int kPlanUnit = 128;   // a page pair for each wave of a 4-wave block (kFp4d64p2: two for every other wave)
+// Partitions of less than 2048 tokens only where 512 blocks would not come
+// together otherwise: a block's fixed cost weighs on them (8 kv heads, without
+// this bound and with it: 128k among 255 contexts of 200 tokens 69.5 / 55.2 us, 10 of
+// 50k among 190 of 300 tokens 131 / 123, 130 lognormal ones around 4k 170.7 / 166).
+constexpr int kPlanShort = 16;
 // PER: the most sequences a lane holds, 1 for batches of up to 64 (their own
 // code path: every block runs it once, from a cold instruction cache).
 template <int PER>
@@ -964,6 +968,9 @@ __device__ __forceinline__ SplitPlan<PER> split_plan(const DecodeParams& p, int 
     const int all = __builtin_amdgcn_readlane(wave_scan(tokens), 63);
     const float sum = float(all) * (1.0f / kPlanUnit);
     int lo = int(sum * p.plan_inv_rows + 0.99f);
+    int least = int(float(all) * p.plan_fill);
+    least = least < kPlanShort ? least : kPlanShort;
+    lo = lo > least ? lo : least;
     lo = lo > 1 ? lo : 1;
     const int whole = (p.max_context + kPlanUnit - 1) / kPlanUnit;   // one partition per sequence
     int hi = whole;

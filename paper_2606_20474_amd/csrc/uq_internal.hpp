@@ -29,6 +29,9 @@ struct TqTables {
 };
 constexpr int kNumCus = 256;     // compute units of an MI355X (8 XCDs x 32)
 constexpr int kPlanBatch = 256;  // sequences a balanced split can hold
+// Granule of the balanced split in tokens: a page pair for each wave of a
+// 4-wave block (kFp4d64p2: two for every other wave).
+constexpr int kPlanUnit = 128;
 constexpr int kTqBlock = 2368;   // bytes per (page, kv head) of the Ultra-TQ cache
 constexpr int kTqMeta = 2048;    // offset of the norms and (scale, zero) words in a block
 
@@ -130,6 +133,7 @@ struct DecodeParams {
     int32_t plan_rows;
     float plan_inv_rows;
     float plan_inv_free;
+    float plan_fill;         // planner units of 512 blocks' equal shares per token
     // partitions per sequence where the lengths are equal, and its reciprocal (0:
     // no rule of their own)
     int32_t plan_equal;

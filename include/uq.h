@@ -187,9 +187,9 @@ int32_t uq_default_partition(const uq_cache_desc *desc, int32_t batch, int32_t n
  * merge.  With the default partition (0, or its value), more than one of
  * them, no shared prefix and up to 256 sequences, the launch instead takes a
  * block grid that shares its rows among the sequences by their lengths, read on the device:
- * the kernels cut every context into partitions of one length, near the
- * shortest for which the rows suffice, so that a ragged batch, or one far below
- * max_context, still fills the GPU.  The result does not depend on the grid
+ * the kernels cut every context into partitions of one length for the whole
+ * batch, short enough that a ragged batch, or one far below max_context, still
+ * fills the GPU and long enough that the rows suffice.  The result does not depend on the grid
  * beyond rounding.  With the balanced split that rounding, and so the bits of a
  * sequence's output, depends on the lengths of the other sequences in the call;
  * any other partition_tokens cuts a context by its own length alone.

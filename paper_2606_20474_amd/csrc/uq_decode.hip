@@ -872,7 +872,8 @@ __device__ __forceinline__ uint32_t fold_words(const R& r) {
 // workspace; how the sequences share them is decided on the device from the
 // context lengths: a partition P (a multiple of kPlanUnit) with sum over
 // sequences of ceil(tokens / P) <= plan_rows, near the shortest such (at most 7
-// bisection candidates are tried), rows handed out sequence after sequence.  With one partition length per launch, sized from
+// bisection candidates are tried) but no shorter than fills the chip (kPlanShort),
+// rows handed out sequence after sequence.  With one partition length per launch, sized from
 // the host's bound of the lengths, the rows of short contexts went unused and
 // the longest partitions ran alone at the end.  Step before / after, one
 // MI355X: 12 sequences of 0.3k-55k tokens under a 64k bound (48/8 heads)

@@ -117,7 +117,8 @@ int32_t equal_parts(int32_t batch, int32_t block_heads, int32_t rows) {
             best_rounds = rounds;
         }
     }
-    return best;
+    // as many as fit, two blocks per CU: what the planner's search finds by itself
+    return best == rows / batch && best_rounds <= 2 ? 0 : best;
 }
 
 // Workspace of a decode call: the partial rows (accumulators, then the

@@ -78,8 +78,9 @@ int64_t num_partitions(int32_t max_context, int32_t part) {
 // few (a single 120k context, 8 kv heads: 27.6 us with 512 blocks, 28.7 with
 // its 472 default partitions, 33 with 944); four rows per sequence where they
 // alone fill the chip (64 sequences of 0.3k-64k tokens, 8 kv heads: 128 us with
-// 2048 blocks, 130 with 1024, 269 with 512).  Two, three, four and six rows per
-// sequence, lognormal lengths of spread s around a median, us:
+// 2048 blocks, 130 with 1024, 269 with 512), as long as that is no more than 20
+// blocks per CU, and two beyond.  Two, three, four and six rows per sequence,
+// lognormal lengths of spread s around a median, us:
 //   128 around 32k, s 0.8, 8 kv heads 1050 1027 1011 1031   (wave grid 1356)
 //   140 around 40k, s 1.0, 8 kv heads 1463 1382 1367 1380   (1569)
 //   256 around 40k, s 0.3, 4 kv heads 1031  984  981  991   (1129)
@@ -87,13 +88,18 @@ int64_t num_partitions(int32_t max_context, int32_t part) {
 //   256 around 16k, s 0.8, 8 kv heads 1023 1025 1034 1065   (1330)
 //   200 around  8k, s 0.3, 8 kv heads  337  338  338  338   (325: one partition of
 //   16384 and a short rest each, the rests last, which fill the end better)
+// FP8 cache, 256 around 16k, 8 kv heads: 1832 with two, 1845 with 20 blocks per CU,
+// 1875 with four.
 // The planner's lanes hold 256 lengths, whose sum and rounding stay within 30 bits.
 int32_t split_rows(int32_t batch, int32_t block_heads, int32_t max_context, int32_t part) {
     const int64_t np = num_partitions(max_context, part);
     if (np <= 1 || part != pick_partition(batch, block_heads, max_context)) return 0;
     if (batch > uq::kPlanBatch || int64_t(batch) * max_context >= (int64_t(1) << 30)) return 0;
+    int64_t each4 = 20 * uq::kNumCus / block_heads;   // four per sequence, up to 20 blocks per CU ...
+    each4 = each4 < 4 * int64_t(batch) ? each4 : 4 * int64_t(batch);
+    const int64_t each = each4 > 2 * int64_t(batch) ? each4 : 2 * int64_t(batch);   // ... but two
     int64_t rows = 2 * uq::kNumCus / block_heads;
-    rows = rows > 4 * int64_t(batch) ? rows : 4 * int64_t(batch);
+    rows = rows > each ? rows : each;
     return int32_t(rows < np * batch ? rows : np * batch);
 }
 

@@ -877,9 +877,9 @@ __device__ __forceinline__ uint32_t fold_words(const R& r) {
 // the host's bound of the lengths, the rows of short contexts went unused and
 // the longest partitions ran alone at the end.  Step before / after, one
 // MI355X: 12 sequences of 0.3k-55k tokens under a 64k bound (48/8 heads)
-// 71 / 44 us; 64 sequences of 0.3k-64k (64/8 heads) 203 / 134 us; 128 of 4k-128k
-// (48/8 heads, the wave grid before) 871 / 682 us; equal lengths unchanged (32 x
-// 32k, 64/4 heads: 100 us).
+// 71 / 44 us; 64 sequences of 0.3k-64k (64/8 heads) 203 / 134 us; 128 lognormal
+// ones around 32k (64/8 heads, the wave grid before) 1154 / 938 us; 32 equal ones of
+// 32k (64/4 heads) 100 / 99 us.
 //
 // Lengths within 1/16 of their maximum (on average) are cut into plan_equal
 // equal parts each (equal_parts in uq_api.hip).

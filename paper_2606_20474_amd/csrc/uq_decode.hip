@@ -872,8 +872,8 @@ __device__ __forceinline__ uint32_t fold_words(const R& r) {
 // workspace; how the sequences share them is decided on the device from the
 // context lengths: a partition P (a multiple of kPlanUnit) with sum over
 // sequences of ceil(tokens / P) <= plan_rows, near the shortest such (at most 7
-// bisection candidates are tried) but no shorter than fills the chip (kPlanShort),
-// rows handed out sequence after sequence.  With one partition length per launch, sized from
+// bisection candidates are tried) but no shorter than fills the chip (kPlanShort).
+// With one partition length per launch, sized from
 // the host's bound of the lengths, the rows of short contexts went unused and
 // the longest partitions ran alone at the end.  Step before / after, one
 // MI355X: 12 sequences of 0.3k-55k tokens under a 64k bound (48/8 heads)
@@ -1013,23 +1013,83 @@ __device__ __forceinline__ SplitPlan<PER> split_plan(const DecodeParams& p, int 
     return s;
 }
 
-// The sequence of row `row` (< total), its tokens and the row's partition of
-// it.
+// Lanes below this one among the set ones of mask.
+__device__ __forceinline__ int lanes_below(uint64_t mask) {
+    return __builtin_amdgcn_mbcnt_hi(uint32_t(mask >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0));
+}
+
+// The work of block `row` (< total) of a kv head: its sequence b and the tokens n of it, the
+// partition, and its partial row.  Partial rows are numbered sequence after
+// sequence, but the blocks take the whole partitions first, then the shorter last
+// ones of the sequences, the longest first (in 32 classes; empty contexts at the end):
+// blocks reach the CUs in this order, so those that get a block more than the others
+// get a short one.  Fixed partitions / sequence after sequence / so, us, lognormal
+// lengths of spread 0.2: 80 around 20k, 4 kv heads, FP4 171 / 196 / 163, FP8
+// cache 282 / 356 / 282, BF16 cache 546 / 729 / 521; 40 around 20k, 8 kv heads, BF16 564 / 668 /
+// 522; FP4, 48 around 60k (0.3), 8 heads 582 / 590 / 547.
 template <int PER>
-__device__ __forceinline__ void plan_row(const SplitPlan<PER>& s, int row, int& b, int& part, int& n) {
-    const int L = __builtin_ctzll(__builtin_amdgcn_ballot_w64(s.scan > row));
-    int first = L > 0 ? __builtin_amdgcn_readlane(s.scan, L > 0 ? L - 1 : 0) : 0;
+__device__ __forceinline__ void plan_row(const DecodeParams& p, const SplitPlan<PER>& s, int lane, int row, int& b, int& part,
+                                         int& n, int& prow) {
+    uint64_t rests[PER];   // lanes whose i-th sequence ends in a shorter partition
+    int cls[PER], upto = s.scan, whole = s.total;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int rest = s.n[i] - (plan_parts(s.n[i], s.part, s.inv) - 1) * s.part;
+        const bool is = (PER == 1 || i < s.per) && lane * s.per + i < p.batch && rest < s.part;
+        rests[i] = __builtin_amdgcn_ballot_w64(is);
+        cls[i] = int(float(rest) * s.inv * 32.0f);
+        upto -= lanes_below(rests[i]) + (is ? 1 : 0);   // whole partitions up to and including this lane's
+        whole -= __builtin_popcountll(rests[i]);
+    }
+    const bool last = row >= whole;
+    uint64_t lanes = __builtin_amdgcn_ballot_w64(upto > row);   // the sequence's lane is the first of these
+    int at = row, seq = 0;                                      // (last) and its sequence of the lane
+    if (last) {
+        // number row - whole in the classes' descending order, one bit of the class after the other
+        at = row - whole;
+#pragma unroll 1
+        for (int bit = 16; bit > 0; bit >>= 1) {
+            uint64_t one[PER];
+            int c = 0;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                one[i] = rests[i] & __builtin_amdgcn_ballot_w64((cls[i] & bit) != 0);
+                c += __builtin_popcountll(one[i]);
+            }
+            const bool in = at < c;
+            at -= in ? 0 : c;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) rests[i] = in ? one[i] : rests[i] & ~one[i];
+        }
+        uint64_t mask = rests[0];
+#pragma unroll
+        for (int i = 1; i < PER; ++i) {
+            const int c = __builtin_popcountll(mask);
+            const bool next = seq == i - 1 && at >= c;
+            at -= next ? c : 0;
+            mask = next ? rests[i] : mask;
+            seq = next ? i : seq;
+        }
+        lanes = mask & __builtin_amdgcn_ballot_w64(lanes_below(mask) == at);
+    }
+    const int L = __builtin_ctzll(lanes), before = L > 0 ? L - 1 : 0;
+    int first = L > 0 ? __builtin_amdgcn_readlane(upto, before) : 0;
+    prow = L > 0 ? __builtin_amdgcn_readlane(s.scan, before) : 0;
     b = L * s.per;
     n = __builtin_amdgcn_readlane(s.n[0], L);
+    int k = plan_parts(n, s.part, s.inv);
 #pragma unroll
     for (int i = 1; i < PER; ++i) {
-        const int k = plan_parts(n, s.part, s.inv);
-        if (i >= s.per || row < first + k) break;
-        first += k;
+        const int w = n < k * s.part ? k - 1 : k;
+        if (last ? i > seq : i >= s.per || row < first + w) break;
+        first += w;
+        prow += k;
         b += 1;
         n = __builtin_amdgcn_readlane(s.n[i], L);
+        k = plan_parts(n, s.part, s.inv);
     }
-    part = row - first;
+    part = last ? k - 1 : row - first;
+    prow += part;
 }
 
 // The first row of sequence b, and its tokens.
@@ -1047,14 +1107,15 @@ __device__ __forceinline__ int plan_first_row(const SplitPlan<PER>& s, int b, in
     return first;
 }
 
-// Row `row` of the balanced split: its sequence, partition and partition
-// length and the sequence's tokens; false for a row that is not in use.
+// Block `row` of the balanced split: as plan_row, and the partition length; false
+// for a block without work.
 template <int PER>
-__device__ __forceinline__ bool plan_of_row(const DecodeParams& p, int lane, int row, int& b, int& part, int& n, int& len) {
+__device__ __forceinline__ bool plan_of_row(const DecodeParams& p, int lane, int row, int& b, int& part, int& n, int& len,
+                                            int& prow) {
     const SplitPlan<PER> s = split_plan<PER>(p, lane);
     len = s.part;
     if (row >= s.total) return false;
-    plan_row(s, row, b, part, n);
+    plan_row(p, s, lane, row, b, part, n, prow);
     return true;
 }
 
@@ -1140,10 +1201,11 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
     int part, first_part;                // this wave's partition, the block's first
     int start, end, ctx = 0;
     bool in_place = false;               // the context is held by this block alone and finished in place
+    int plan_prow = 0;                   // balanced split: the block's partial row
     if (plan) {
         int len;
-        if (!(p.batch <= 64 ? plan_of_row<1>(p, lane, row, b, part, ctx, len)
-                            : plan_of_row<4>(p, lane, row, b, part, ctx, len)))
+        if (!(p.batch <= 64 ? plan_of_row<1>(p, lane, row, b, part, ctx, len, plan_prow)
+                            : plan_of_row<4>(p, lane, row, b, part, ctx, len, plan_prow)))
             return;
         first_part = part;
         start = part * len;
@@ -1793,7 +1855,7 @@ __attribute__((amdgpu_waves_per_eu(occupancy<F, S, W>(), occupancy<F, S, W>())))
             // the wave grid: one slot per block of W partitions
             const int slot = pre ? p.suffix_partitions + part : WP ? first_part / W : part;
             // (balanced split: the partial rows are [row][Hq])
-            const int64_t prow = plan ? int64_t(row) * p.num_q_heads + hq
+            const int64_t prow = plan ? int64_t(plan_prow) * p.num_q_heads + hq
                                       : (int64_t(rb) * p.num_q_heads + hq) * p.num_partitions + slot;
             float4* dst = reinterpret_cast<float4*>(p.part_acc + prow * D + N * L);
 #pragma unroll
@@ -2350,7 +2412,7 @@ __device__ __forceinline__ int list_long_rows(const DecodeParams& p, const Split
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
         const uint64_t longs = __builtin_amdgcn_ballot_w64(k[i] > kLongRow);
-        const int at = count + __builtin_amdgcn_mbcnt_hi(uint32_t(longs >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(longs), 0));
+        const int at = count + lanes_below(longs);
         if (k[i] > kLongRow) list[at] = make_int2(first, k[i] * 256 + lane * s.per + i);
         count += __builtin_popcountll(longs);
         first += k[i];

@@ -356,10 +356,15 @@ int32_t ref_fmt(const uq_ref_cache_desc* d) {
 
 // The cache format of a decode call's parameter block (both of its launches).
 // Ultra-TQ is bound by each CU's decoding, which more and smaller blocks spread
-// better than equal parts do (128 x 20k, 8 kv heads 626 us, 639 with them).
+// better than equal parts do (128 x 20k, 8 kv heads 626 us, 639 with them).  The
+// BF16 cache has two blocks resident per CU, not four: a third equal one runs alone
+// when both have ended, a short last partition starts earlier.  Equal parts /
+// whole partitions of the default length and a rest each, us: 48 x 20k, 8 heads 656 /
+// 614; 40 x 30k, 8 heads 892 / 813; 24 x 20k, 8 heads 306 / 297; 48 x 10k, 8 heads 334 / 313.
 void set_ref_format(const uq_ref_cache_desc* d, uq::DecodeParams& p) {
     p.kv_fmt = ref_fmt(d);
     if (p.kv_fmt == uq::kTq4) p.plan_equal = 0;
+    if (p.kv_fmt == uq::kBf16 && p.plan_equal > 0) p.plan_equal = -1;
 }
 
 // Half of the bytes of one (page, kv head): the K tile, or for TQ4 half of

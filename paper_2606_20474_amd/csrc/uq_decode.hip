@@ -882,7 +882,7 @@ __device__ __forceinline__ uint32_t fold_words(const R& r) {
 // 32k (64/4 heads) 100 / 99 us.
 //
 // Lengths within 1/16 of their maximum (on average) are cut into plan_equal
-// equal parts each (equal_parts in uq_api.hip).
+// equal parts each (equal_parts in uq_api.hip), or (-1) at the default partition.
 //
 // Every wave computes the plan for itself (lane l holds sequences l * per ..
 // l * per + per - 1, per <= 4): the sums and the scan are DPP.  The search
@@ -982,10 +982,13 @@ __device__ __forceinline__ SplitPlan<PER> split_plan(const DecodeParams& p, int 
     // lo, once tried, does not fit; hi does (`whole` for certain); s keeps the
     // last candidate that fitted, which is hi when the loop ends
     int cand = lo;
-    if (p.plan_equal > 0) {
+    if (p.plan_equal != 0) {
         const int top = wave_max(most);
-        if (int64_t(all) * 16 >= int64_t(p.batch) * top * 15)
-            cand = plan_parts((top + kPlanUnit - 1) / kPlanUnit, p.plan_equal, p.plan_inv_equal);
+        if (int64_t(all) * 16 >= int64_t(p.batch) * top * 15) {
+            const int fixed = p.partition_tokens / kPlanUnit;
+            cand = p.plan_equal > 0 ? plan_parts((top + kPlanUnit - 1) / kPlanUnit, p.plan_equal, p.plan_inv_equal)
+                                    : fixed > lo ? fixed : lo;
+        }
     }
 #pragma unroll 1
     for (int it = 0;; ++it) {

@@ -135,7 +135,7 @@ struct DecodeParams {
     float plan_inv_free;
     float plan_fill;         // planner units of 512 blocks' equal shares per token
     // partitions per sequence where the lengths are equal, and its reciprocal (0:
-    // no rule of their own)
+    // no rule of their own; -1: partitions of partition_tokens)
     int32_t plan_equal;
     float plan_inv_equal;
     int32_t merge_by_head;   // merge launch: a block's query heads belong to one kv head

@@ -81,15 +81,12 @@ int64_t num_partitions(int32_t max_context, int32_t part) {
 // 2048 blocks, 130 with 1024, 269 with 512), as long as that is no more than 20
 // blocks per CU, and two beyond.  Two, three, four and six rows per sequence,
 // lognormal lengths of spread s around a median, us:
-//   128 around 32k, s 0.8, 8 kv heads 1050 1027 1011 1031   (wave grid 1356)
-//   140 around 40k, s 1.0, 8 kv heads 1463 1382 1367 1380   (1569)
-//   256 around 40k, s 0.3, 4 kv heads 1031  984  981  991   (1129)
-//   160 around 40k, s 0.3, 8 kv heads 1214 1193 1183 1202   (1364)
-//   256 around 16k, s 0.8, 8 kv heads 1023 1025 1034 1065   (1330)
-//   200 around  8k, s 0.3, 8 kv heads  337  338  338  338   (325: one partition of
-//   16384 and a short rest each, the rests last, which fill the end better)
-// FP8 cache, 256 around 16k, 8 kv heads: 1832 with two, 1845 with 20 blocks per CU,
-// 1875 with four.
+//   100 around 30k, s 0.3, 4 kv heads  310  298  300  298   (wave grid 326)
+//   128 around 32k, s 0.8, 8 kv heads 1004 1000 1010 1010   (1380)
+//   140 around 40k, s 1.0, 8 kv heads 1385 1388 1396 1409   (1630)
+//   256 around 40k, s 0.3, 4 kv heads  939  944  940  945   (1150)
+//   256 around 16k, s 0.8, 8 kv heads  993  984  986  997   (1330)
+// FP8 cache, 256 around 16k, 8 kv heads 1797 1792 1800 1814; Ultra-TQ 1173 1159 1161 1168.
 // The planner's lanes hold 256 lengths, whose sum and rounding stay within 30 bits.
 int32_t split_rows(int32_t batch, int32_t block_heads, int32_t max_context, int32_t part) {
     const int64_t np = num_partitions(max_context, part);
@@ -209,8 +206,12 @@ uq_status make_decode_params(const uq_cache_desc* desc, const void* q, uq_dtype 
     p.plan_rows = extra_slots > 0 ? 0 : split_rows(batch, block_heads(desc, num_q_heads), max_context, part);
     p.plan_inv_rows = p.plan_rows > 0 ? 1.0f / float(p.plan_rows) : 0.0f;
     p.plan_inv_free = p.plan_rows > batch ? 1.0f / float(p.plan_rows - batch) : 0.0f;
-    p.plan_fill = float(block_heads(desc, num_q_heads)) / float(2 * uq::kNumCus * uq::kPlanUnit);
     p.plan_equal = equal_parts(batch, block_heads(desc, num_q_heads), p.plan_rows);
+    p.plan_fill = float(block_heads(desc, num_q_heads)) / float(2 * uq::kNumCus * uq::kPlanUnit);
+    // a tenth longer, so that the rests still fit into two blocks per CU, except where
+    // equal lengths give exactly that (without / with it, us: 32 x 32k, 4 heads
+    // 98.5 / 103.3; BF16 cache, 40 around 20k, s 0.2, 4 heads 286 / 260, FP8 144 / 136)
+    if (p.plan_equal != 0) p.plan_fill *= 1.1f;
     p.plan_inv_equal = p.plan_equal > 0 ? 1.0f / float(p.plan_equal) : 0.0f;
     p.merge_by_head = 0;
     p.long_blocks = 0;

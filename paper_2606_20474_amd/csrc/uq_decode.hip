@@ -889,11 +889,14 @@ __device__ __forceinline__ uint32_t fold_words(const R& r) {
 // tries the lower bound sum / plan_rows first (the answer for equal lengths),
 // then halves the range up to sum / (plan_rows - batch), which always fits.  An
 // empty context keeps one row (its zero output).
-// Partitions of less than 2048 tokens only where 512 blocks would not come
-// together otherwise: a block's fixed cost weighs on them (8 kv heads, without
-// this bound and with it: 128k among 255 contexts of 200 tokens 69.5 / 55.2 us, 10 of
-// 50k among 190 of 300 tokens 131 / 123, 130 lognormal ones around 4k 170.7 / 166).
-constexpr int kPlanShort = 16;
+// Partitions of less than kPlanShort units (13824 tokens) only where two blocks per CU would
+// not come together otherwise (plan_fill): a block's fixed cost weighs on them, and
+// its partial has to be merged.  A bound of 2048 tokens / this, us: lognormal lengths, 130
+// around 8k (s 0.8), 8 kv heads, FP8 cache 474 / 450; 256 around 3k (0.8), 16 heads 428 / 394; 200 around
+// 12k (0.5), 8 heads 497 / 481; 20 around 40k (0.2), 8 heads, FP8 276 / 256, BF16 cache 609 / 515; 10 of 50k
+// among 90 of 300 tokens, 8 heads 112 / 107; but 120k among 31 of 1k 36.2 / 37.7.  Bounds of 8192 to
+// 27648 differ by 1 to 2 %.
+constexpr int kPlanShort = 108;
 // PER: the most sequences a lane holds, 1 for batches of up to 64 (their own
 // code path: every block runs it once, from a cold instruction cache).
 template <int PER>

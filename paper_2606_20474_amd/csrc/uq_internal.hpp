@@ -133,7 +133,7 @@ struct DecodeParams {
     int32_t plan_rows;
     float plan_inv_rows;
     float plan_inv_free;
-    float plan_fill;         // planner units of 512 blocks' equal shares per token
+    float plan_fill;         // planner units of about 512 blocks' equal shares per token
     // partitions per sequence where the lengths are equal, and its reciprocal (0:
     // no rule of their own; -1: partitions of partition_tokens)
     int32_t plan_equal;

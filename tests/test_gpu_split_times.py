@@ -19,6 +19,8 @@ def lognormal(batch, median, sigma):
     ("fp8", lognormal(80, 20000, 0.2), 4),    # 1.28, 0.99
     ("bf16", lognormal(80, 20000, 0.2), 4),   # 1.40, 0.96
     ("bf16", lognormal(40, 20000, 0.2), 8),   # 1.24, 0.94
+    ("bf16", lognormal(20, 40000, 0.2), 8),   # 1.20, 0.96
+    ("bf16", lognormal(40, 20000, 0.2), 4),   # 1.21, 0.97
     ("bf16", [30000] * 40, 8),                # 1.09, 1.00
 ])
 def test_split_is_no_slower_than_fixed_partitions(fmt, ctx, hkv):

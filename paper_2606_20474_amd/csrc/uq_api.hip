@@ -213,6 +213,7 @@ uq_status make_decode_params(const uq_cache_desc* desc, const void* q, uq_dtype 
     // 98.5 / 103.3; BF16 cache, 40 around 20k, s 0.2, 4 heads 286 / 260, FP8 144 / 136)
     if (p.plan_equal != 0) p.plan_fill *= 1.1f;
     p.plan_inv_equal = p.plan_equal > 0 ? 1.0f / float(p.plan_equal) : 0.0f;
+    p.plan_order = p.plan_equal != 0;
     p.merge_by_head = 0;
     p.long_blocks = 0;
     p.probe_sink = nullptr;

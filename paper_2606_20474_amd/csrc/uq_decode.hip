@@ -1029,13 +1029,32 @@ __device__ __forceinline__ int lanes_below(uint64_t mask) {
 // sequence, but the blocks take the whole partitions first, then the shorter last
 // ones of the sequences, the longest first (in 32 classes; empty contexts at the end):
 // blocks reach the CUs in this order, so those that get a block more than the others
-// get a short one.  Fixed partitions / sequence after sequence / so, us, lognormal
+// get a short one.  Sequence after sequence, in code of its own, where plan_order is 0:
+// two blocks per CU or fewer, for which the order is no gain and costs a step of 1531
+// tokens 0.45 us of 13.3, of 12 ragged sequences 1.0 of 42.8.  Fixed partitions / sequence after sequence / so, us, lognormal
 // lengths of spread 0.2: 80 around 20k, 4 kv heads, FP4 171 / 196 / 163, FP8
 // cache 282 / 356 / 282, BF16 cache 546 / 729 / 521; 40 around 20k, 8 kv heads, BF16 564 / 668 /
 // 522; FP4, 48 around 60k (0.3), 8 heads 582 / 590 / 547.
 template <int PER>
 __device__ __forceinline__ void plan_row(const DecodeParams& p, const SplitPlan<PER>& s, int lane, int row, int& b, int& part,
                                          int& n, int& prow) {
+    if (__builtin_expect(p.plan_order == 0, 1)) {
+        const int L = __builtin_ctzll(__builtin_amdgcn_ballot_w64(s.scan > row));
+        int first = L > 0 ? __builtin_amdgcn_readlane(s.scan, L > 0 ? L - 1 : 0) : 0;
+        b = L * s.per;
+        n = __builtin_amdgcn_readlane(s.n[0], L);
+#pragma unroll
+        for (int i = 1; i < PER; ++i) {
+            const int k = plan_parts(n, s.part, s.inv);
+            if (i >= s.per || row < first + k) break;
+            first += k;
+            b += 1;
+            n = __builtin_amdgcn_readlane(s.n[i], L);
+        }
+        part = row - first;
+        prow = row;
+        return;
+    }
     uint64_t rests[PER];   // lanes whose i-th sequence ends in a shorter partition
     int cls[PER], upto = s.scan, whole = s.total;
 #pragma unroll

@@ -138,6 +138,7 @@ struct DecodeParams {
     // no rule of their own; -1: partitions of partition_tokens)
     int32_t plan_equal;
     float plan_inv_equal;
+    int32_t plan_order;      // blocks of short partitions after the whole ones
     int32_t merge_by_head;   // merge launch: a block's query heads belong to one kv head
     int32_t long_blocks;     // merge launch: blocks of the split's long rows, ahead of the others
     // the page-gather probe's checksums, one per wave of the partition

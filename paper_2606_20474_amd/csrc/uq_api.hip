@@ -107,7 +107,7 @@ int32_t split_rows(int32_t batch, int32_t block_heads, int32_t max_context, int3
 // busy) / k.  Batches whose rows allow more than 8 come out even without.  Most parts
 // that fit / this, one MI355X, 8 query heads per KV head: 36 x 100k, 4 kv heads
 // 364 / 320 us; 150 x 40k, 4 heads 552 / 527; 48 x 40k, 8 heads 348 / 330; 160 x 30k, 8
-// heads 854 / 834; BF16 cache, 36 x 50k, 4 heads 692 / 544.
+// heads 854 / 834.
 int32_t equal_parts(int32_t batch, int32_t block_heads, int32_t rows) {
     if (rows / batch > 8) return 0;
     int32_t best = 0;
@@ -214,6 +214,7 @@ uq_status make_decode_params(const uq_cache_desc* desc, const void* q, uq_dtype 
     if (p.plan_equal != 0) p.plan_fill *= 1.1f;
     p.plan_inv_equal = p.plan_equal > 0 ? 1.0f / float(p.plan_equal) : 0.0f;
     p.plan_order = p.plan_equal != 0;
+    p.plan_short = uq::kPlanShort;
     p.merge_by_head = 0;
     p.long_blocks = 0;
     p.probe_sink = nullptr;
@@ -366,7 +367,10 @@ int32_t ref_fmt(const uq_ref_cache_desc* d) {
 void set_ref_format(const uq_ref_cache_desc* d, uq::DecodeParams& p) {
     p.kv_fmt = ref_fmt(d);
     if (p.kv_fmt == uq::kTq4) p.plan_equal = 0;
-    if (p.kv_fmt == uq::kBf16 && p.plan_equal > 0) p.plan_equal = -1;
+    if (p.kv_fmt == uq::kBf16) {
+        p.plan_short = 64;
+        if (p.plan_equal > 0) p.plan_equal = -1;
+    }
 }
 
 // Half of the bytes of one (page, kv head): the K tile, or for TQ4 half of

@@ -894,9 +894,10 @@ __device__ __forceinline__ uint32_t fold_words(const R& r) {
 // its partial has to be merged.  A bound of 2048 tokens / this, us: lognormal lengths, 130
 // around 8k (s 0.8), 8 kv heads, FP8 cache 474 / 450; 256 around 3k (0.8), 16 heads 428 / 394; 200 around
 // 12k (0.5), 8 heads 497 / 481; 20 around 40k (0.2), 8 heads, FP8 276 / 256, BF16 cache 609 / 515; 10 of 50k
-// among 90 of 300 tokens, 8 heads 112 / 107; but 120k among 31 of 1k 36.2 / 37.7.  Bounds of 8192 to
-// 27648 differ by 1 to 2 %.
-constexpr int kPlanShort = 108;
+// among 90 of 300 tokens, 8 heads 112 / 107; but 120k among 31 of 1k 36.2 / 37.7.  A bound of 8192 is
+// up to 2 % slower (256 around 20k, s 0.3, 8 heads 960 / 939).  The BF16 cache, two
+// blocks resident per CU, takes 8192 (plan_short) where it gets more of them (64 around 20k, s 0.3, 8
+// heads 917 with 13824, 895 with 8192; 150 around 20k, s 0.2, 4 heads 952 / 928).
 // PER: the most sequences a lane holds, 1 for batches of up to 64 (their own
 // code path: every block runs it once, from a cold instruction cache).
 template <int PER>
@@ -973,7 +974,7 @@ __device__ __forceinline__ SplitPlan<PER> split_plan(const DecodeParams& p, int 
     const float sum = float(all) * (1.0f / kPlanUnit);
     int lo = int(sum * p.plan_inv_rows + 0.99f);
     int least = int(float(all) * p.plan_fill);
-    least = least < kPlanShort ? least : kPlanShort;
+    least = least <= kPlanShort ? least : p.plan_short;
     lo = lo > least ? lo : least;
     lo = lo > 1 ? lo : 1;
     const int whole = (p.max_context + kPlanUnit - 1) / kPlanUnit;   // one partition per sequence
@@ -1031,10 +1032,10 @@ __device__ __forceinline__ int lanes_below(uint64_t mask) {
 // blocks reach the CUs in this order, so those that get a block more than the others
 // get a short one.  Sequence after sequence, in code of its own, where plan_order is 0:
 // two blocks per CU or fewer, for which the order is no gain and costs a step of 1531
-// tokens 0.45 us of 13.3, of 12 ragged sequences 1.0 of 42.8.  Fixed partitions / sequence after sequence / so, us, lognormal
-// lengths of spread 0.2: 80 around 20k, 4 kv heads, FP4 171 / 196 / 163, FP8
-// cache 282 / 356 / 282, BF16 cache 546 / 729 / 521; 40 around 20k, 8 kv heads, BF16 564 / 668 /
-// 522; FP4, 48 around 60k (0.3), 8 heads 582 / 590 / 547.
+// tokens 0.45 us of 13.3, of 12 ragged sequences 1.0 of 42.8.  Fixed partitions /
+// sequence after sequence / so, us, lognormal lengths of spread 0.2: 80 around 20k, 4
+// kv heads, FP4 171 / 196 / 163, FP8 cache 282 / 356 / 282, BF16 cache 546 / 729 / 521; 40
+// around 20k, 8 kv heads, BF16 564 / 668 / 522; FP4, 48 around 60k (0.3), 8 heads 582 / 590 / 547.
 template <int PER>
 __device__ __forceinline__ void plan_row(const DecodeParams& p, const SplitPlan<PER>& s, int lane, int row, int& b, int& part,
                                          int& n, int& prow) {

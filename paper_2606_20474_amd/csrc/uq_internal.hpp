@@ -32,6 +32,7 @@ constexpr int kPlanBatch = 256;  // sequences a balanced split can hold
 // Granule of the balanced split in tokens: a page pair for each wave of a
 // 4-wave block (kFp4d64p2: two for every other wave).
 constexpr int kPlanUnit = 128;
+constexpr int kPlanShort = 108;  // units of a partition that is long enough (see SplitPlan in uq_decode.hip)
 constexpr int kTqBlock = 2368;   // bytes per (page, kv head) of the Ultra-TQ cache
 constexpr int kTqMeta = 2048;    // offset of the norms and (scale, zero) words in a block
 
@@ -133,6 +134,7 @@ struct DecodeParams {
     int32_t plan_rows;
     float plan_inv_rows;
     float plan_inv_free;
+    int32_t plan_short;      // least planner units of a partition where there are more blocks than two per CU
     float plan_fill;         // planner units of about 512 blocks' equal shares per token
     // partitions per sequence where the lengths are equal, and its reciprocal (0:
     // no rule of their own; -1: partitions of partition_tokens)
